@@ -2217,6 +2217,7 @@ hipError_t launch_decode(const Geo& g, const void* plan, const void* y_agg, cons
         if (e != hipSuccess) return e;
         b_agg = cand;
     }
+    if (whole_decode_fits(g)) return launch_decode_whole(g, plan, y_agg, b_agg, out, L.cap, s);
     if (g.f32) return launch_decode_t<float>(g, plan, y_agg, b_agg, out, L, ws, s);
     return launch_decode_t<int32_t>(g, plan, y_agg, b_agg, out, L, ws, s);
 }

@@ -139,6 +139,13 @@ hipError_t launch_decode(const Geo& g, const void* plan, const void* y_agg,
 hipError_t launch_decode_blocked(const Geo& g, const void* y_agg, const uint32_t* b_agg,
                                  const DecodeOut& out, const BlockedLayout& L, void* ws,
                                  hipStream_t s);
+// a global sketch of at most 1024 batches that fits one workgroup's LDS: one
+// launch whose workgroups each peel the whole sketch and write a slice of the
+// outputs (cap: the decode's support bound)
+bool whole_decode_fits(const Geo& g);
+hipError_t launch_decode_whole(const Geo& g, const void* plan, const void* y_agg,
+                               const uint32_t* b_agg, const DecodeOut& out, uint64_t cap,
+                               hipStream_t s);
 // support offsets of the bitmap chunks: blk[i] = set bits before chunk i of
 // kChunkWords words; ctrl is a 64-byte control block that the scan also uses
 hipError_t launch_support_offsets(const Geo& g, const uint32_t* b, uint32_t* blk, void* ctrl,
