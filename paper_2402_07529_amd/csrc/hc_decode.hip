@@ -59,6 +59,15 @@ constexpr uint64_t kPeelHalfGridCells = 8ull << 20;  // below this many cells th
 constexpr uint64_t kPeelHalfGridCellsInt = 32ull << 20;  // the same with residuals in the counters
 constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a packed counter
 
+// The fp32 decode keeps each cell's counter and fp64 residual side by side in
+// one 16-byte record: counter i is 64-bit word 2 i and its residual word
+// 2 i + 1.  The int32 decode keeps two arrays.
+template <typename T> constexpr uint32_t kCellStride = std::is_same<T, double>::value ? 2u : 1u;
+// With at most 2^kPairBits support elements the fp32 peel holds the counters
+// as doubles, deg * 2^k + (sum of positions) < 2^53, always exact (see
+// peel_pairs).
+constexpr uint32_t kPairBits = 26;
+
 // The int32 peel can carry a cell's residual in its counter word: value in
 // the high 32 bits, deg * 2^k + (sum of member positions) in the low 32, with
 // every position below 2^k.  An element leaving the cell subtracts
@@ -136,9 +145,15 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(const T* __restrict__ y_ag
     // do not pack)
     const bool copy = !(std::is_same<T, int32_t>::value && planned);
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < cells; i += step) {
-        if (copy) yw[i] = (typename Acc<T>::type)y_agg[i];
-        if (!planned) cnt[i] = 0ull;
-        if (mark != nullptr) mark[i] = 0u;
+        if constexpr (std::is_same<T, float>::value) {
+            // one 16-byte store per record (with a plan the counter kernel
+            // overwrites the counter)
+            reinterpret_cast<double2*>(cnt)[i] = make_double2(0.0, (double)y_agg[i]);
+            mark[i] = 0u;
+        } else {
+            if (copy) yw[i] = (typename Acc<T>::type)y_agg[i];
+            if (!planned) cnt[i] = 0ull;
+        }
     }
 }
 
@@ -299,6 +314,7 @@ struct SupportArgs {
     Ctrl* ctrl;
     uint64_t words, nchunks, cap, seed;
     uint32_t last_mask, log2wpb, nb, rows, c, cmask, log2c;
+    uint32_t cstride;            // 64-bit words from one counter to the next
     bool vec;  // b is 16-byte aligned
 };
 
@@ -314,7 +330,8 @@ __device__ __forceinline__ void support_put(const SupportArgs& a, uint32_t pos, 
         const uint32_t t = p & a.cmask;
         const unsigned long long inc = kOne + pos;
 #pragma unroll
-        for (int j = 0; j < 3; j++) atomicAdd(a.cnt + cell_of(h, j, t, a.c, a.cmask), inc);
+        for (int j = 0; j < 3; j++)
+            atomicAdd(a.cnt + (uint64_t)a.cstride * cell_of(h, j, t, a.c, a.cmask), inc);
     }
 }
 
@@ -517,6 +534,7 @@ struct CounterArgs {
     Ctrl* ctrl;
     uint64_t n, seed, words, nb;
     uint32_t rows, c, cmask, cells, last_mask;
+    uint32_t cstride;  // 64-bit words from one counter to the next
 };
 
 // One workgroup per sketch row (grid-stride).  Cell k of row r gathers, from
@@ -614,7 +632,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         bool fits = true;
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) {
             const unsigned long long acc = s_acc[k];
-            a.cnt[row * C + k] = acc;
+            a.cnt[(uint64_t)a.cstride * (row * C + k)] = acc;
             fits = fits && fits_packed(acc, kpack);
         }
         flag_unpackable(a.ctrl, fits);
@@ -687,12 +705,12 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
                 }
             }
         }
-        unsigned long long* dst = a.cnt + (uint64_t)row * C;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
         bool fits = true;
 #pragma unroll
         for (uint32_t i = 0; i < CPL; i++) {
             const unsigned long long v = acc[i * 64u + lane];
-            dst[i * 64u + lane] = v;
+            dst[a.cstride * (i * 64u + lane)] = v;
             fits = fits && fits_packed(v, kpack);
         }
         flag_unpackable(a.ctrl, fits);
@@ -850,11 +868,11 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
         build_row<C>(a, row, acc);
-        unsigned long long* dst = a.cnt + (uint64_t)row * C;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
         bool fits = true;
         for (uint32_t k = lane; k < (uint32_t)C; k += 64) {
             const unsigned long long v = acc[k];
-            dst[k] = v;
+            dst[a.cstride * k] = v;
             fits = fits && fits_packed(v, kpack);
         }
         flag_unpackable(a.ctrl, fits);
@@ -1197,12 +1215,26 @@ __device__ __forceinline__ void scan_residual(const PeelArgs<T>& a, uint64_t cid
                        ((unsigned long long)y << 32) | (((v >> 32) << kp) + (v & 0xffffffffull)));
         else
             __hip_atomic_store(a.yw + cidx, (int32_t)y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        // fp32: the residual is in the record already; the counter becomes a double
+        if (!packed || cidx >= a.cells) return;
+        const double d = (double)(((v >> 32) << kp) + (v & 0xffffffffull));
+        st_agent64(a.cnt + 2 * cidx, __builtin_bit_cast(unsigned long long, d));
     }
 }
 
-// One frontier entry (cell cidx, element position pos), for the kernel below.
-// PACKED: int32 residuals ride in the counter words (kp position bits).
-// Sets the (at most two) cells that became pure, with their elements.
+// Whether the peel runs its fused form: int32 with the residuals in the
+// counter words, or fp32 with the counters as doubles.
+template <typename T>
+__device__ __forceinline__ bool peel_packed(const PeelArgs<T>& a, uint32_t kp) {
+    if constexpr (std::is_same<T, int32_t>::value) return a.counted && a.ctrl->nopack == 0;
+    return kp <= kPairBits;
+}
+
+// One frontier entry (cell cidx, element position pos): whether it recovers
+// its element this round, and then the element's value (written), its two
+// other cells oc and the bits of oneg: the signs g of the element in them.
+// PACKED (int32): residuals ride in the counter words.
 // Integer peels (T = int32): the first frontier entry of an element to claim
 // its flag recovers it; any of its pure cells holds the same value exactly.
 // The fp32 gradient's peel (T = double, with marks): every element is
@@ -1214,14 +1246,14 @@ __device__ __forceinline__ void scan_residual(const PeelArgs<T>& a, uint64_t cid
 // element's cells enter the frontier only in the round before it is
 // recovered, so "mark == r + 1" tells exactly which of its cells are pure at
 // the start of round r; the element's entries with a larger j stand aside and
-// no claim is needed.  Its flag, set with a plain store, stops entries of
+// no claim is needed.  Its flag, set with a plain byte store (an atomic OR on
+// its word costs a scattered atomic, three times a store), stops entries of
 // later rounds (a cell of the element that became pure while it was being
 // recovered).
 template <typename T, bool PACKED>
-__device__ __forceinline__ void peel_entry(const PeelArgs<T>& a, uint32_t cidx, uint32_t pos,
-                                           uint32_t kp, uint32_t r, uint32_t& recovered,
-                                           uint32_t& last_round, bool (&push)[2],
-                                           uint32_t (&pcell)[2], uint32_t (&ppos)[2]) {
+__device__ __forceinline__ bool peel_decide(const PeelArgs<T>& a, uint32_t cidx, uint32_t pos,
+                                            uint32_t r, T& val, uint32_t (&oc)[2],
+                                            uint32_t& oneg) {
     constexpr bool kMarks = std::is_same<T, double>::value;
     // the element's flag byte within its 32-bit word (the flags are 256-byte
     // aligned): a byte rather than a word per element keeps the flags a
@@ -1236,7 +1268,8 @@ __device__ __forceinline__ void peel_entry(const PeelArgs<T>& a, uint32_t cidx, 
     unsigned long long wcell = 0;
     T ycell = T(0);
     if (PACKED) wcell = ld_agent64(a.cnt + cidx);
-    else ycell = __hip_atomic_load(a.yw + cidx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else ycell = __hip_atomic_load(a.yw + (uint64_t)kCellStride<T> * cidx, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
     bool taken;
     if (kMarks)
         taken = (__hip_atomic_load(fword, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & fbit) != 0u;
@@ -1257,44 +1290,132 @@ __device__ __forceinline__ void peel_entry(const PeelArgs<T>& a, uint32_t cidx, 
     } else {
         asm volatile("" : : "v"(ycell));
     }
-    if (taken || cl[j] != cidx) return;
+    if (taken || cl[j] != cidx) return false;
     if (kMarks) {
         for (int jj = 0; jj < j; jj++)
             if (__hip_atomic_load(a.mark + cl[jj], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                 r + 1u)
-                return;
-        atomicOr(fword, fbit);  // neighbours' flags share the word
+                return false;
+        __hip_atomic_store(a.peeled + pos, (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (PACKED) ycell = (T)(int32_t)(uint32_t)(wcell >> 32);
-    const T val = Val<T>::sign(ycell, (h.neg >> j) & 1u);
+    val = Val<T>::sign(ycell, (h.neg >> j) & 1u);
     a.vals[pos] = val;
-    recovered++;
-    last_round = r + 1u;
     const int jo[2] = {j == 0 ? 1 : 0, j == 2 ? 1 : 2};
-    unsigned long long old[2], inc[2];
+    oc[0] = cl[jo[0]];
+    oc[1] = cl[jo[1]];
+    oneg = ((h.neg >> jo[0]) & 1u) | (((h.neg >> jo[1]) & 1u) << 1);
+    return true;
+}
+
+// The fp32 peel's updates of one wave's recovered elements (act; every lane of
+// the wave calls it).  A scattered atomic costs the chip the same whether a
+// wave instruction brings one lane or many to its 64-byte line (23 G lines/s
+// measured, whatever the array's size), and the counter is a double beside its
+// residual, so lanes 2 m and 2 m + 1 update both words of one record in one
+// fp64 atomic add: two lines per element instead of four.  Even lanes get the
+// old counter and queue the cell if it became pure.  LSTM-sized fp32 decode
+// (5.1 M elements): 1972 -> 1553 us, with the flags' byte stores.
+template <typename Q>
+__device__ __forceinline__ void peel_pairs(const PeelArgs<double>& a, bool act, uint32_t pos,
+                                           double val, const uint32_t (&oc)[2], uint32_t oneg,
+                                           uint32_t kp, Q& q) {
+    const uint32_t lane = lane_id();
+    const uint64_t acts = __ballot(act);
+    if (acts == 0ull) return;
+    double* const rec = reinterpret_cast<double*>(a.cnt);
+    const bool second = (lane & 1u) != 0u;
+    double old[4], inc[4];
+    uint32_t cell[4];
+    bool on[4];
+    const unsigned long long vbits = __builtin_bit_cast(unsigned long long, val);
 #pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const T gx = Val<T>::sign(val, !((h.neg >> jo[u]) & 1u));  // -g * x
-        if (PACKED)
-            inc[u] = ((unsigned long long)(uint32_t)(int32_t)gx << 32) - ((1ull << kp) + pos);
-        else
-            inc[u] = 0ull - (kOne + pos);
-        old[u] = atomicAdd(a.cnt + cl[jo[u]], inc[u]);
-        if (!PACKED) Val<T>::atomic_add(a.yw + cl[jo[u]], gx);
-    }
+    for (uint32_t h = 0; h < 2; h++) {
+        const uint32_t src = 32u * h + (lane >> 1);
+        const uint32_t spos = (uint32_t)__shfl((int)pos, (int)src);
+        const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)vbits, (int)src);
+        const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(vbits >> 32), (int)src);
+        const uint32_t sneg = (uint32_t)__shfl((int)oneg, (int)src);
+        const double x = __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+        const double leave = -(double)((1ull << kp) + spos);
 #pragma unroll
-    for (int u = 0; u < 2; u++) {
-        const unsigned long long nw = old[u] + inc[u];
-        pcell[u] = cl[jo[u]];
-        if (PACKED) {
-            const uint32_t low = (uint32_t)nw;
-            push[u] = (low >> kp) == 1u;
-            ppos[u] = low & ((1u << kp) - 1u);
-        } else {
-            push[u] = (nw >> 32) == 1ull;
-            ppos[u] = (uint32_t)nw;
+        for (uint32_t u = 0; u < 2; u++) {
+            cell[2 * h + u] = (uint32_t)__shfl((int)oc[u], (int)src);
+            on[2 * h + u] = ((acts >> src) & 1ull) != 0ull;
+            inc[2 * h + u] = second ? Val<double>::sign(x, !((sneg >> u) & 1u)) : leave;
         }
     }
+#pragma unroll
+    for (uint32_t s = 0; s < 4; s++) {
+        old[s] = 0.0;
+        if (on[s])
+            old[s] = unsafeAtomicAdd(rec + 2ull * cell[s] + (second ? 1u : 0u), inc[s]);
+    }
+#pragma unroll
+    for (uint32_t s = 0; s < 4; s++) {
+        const bool first = on[s] && !second;
+        const unsigned long long low = first ? (unsigned long long)(old[s] + inc[s]) : 0ull;
+        lds_push(q, first && (low >> kp) == 1ull, cell[s], (uint32_t)low & ((1u << kp) - 1u));
+    }
+}
+
+// One frontier entry per lane (have), taken by every lane of the wave: the
+// entry's element is recovered if it is the one to do so, leaves its two other
+// cells, and those that became pure are staged for the next frontier.
+template <typename T, typename Q>
+__device__ __forceinline__ void peel_step(const PeelArgs<T>& a, bool have, uint2 it, bool packed,
+                                          uint32_t kp, uint32_t r, uint32_t& recovered,
+                                          uint32_t& last_round, Q& q) {
+    T val = T(0);
+    uint32_t oc[2] = {0u, 0u}, oneg = 0;
+    bool act = false;
+    constexpr bool kInt = std::is_same<T, int32_t>::value;
+    if (have) {
+        if (kInt && packed)
+            act = peel_decide<T, kInt>(a, it.x, it.y, r, val, oc, oneg);
+        else
+            act = peel_decide<T, false>(a, it.x, it.y, r, val, oc, oneg);
+    }
+    if (act) {
+        recovered++;
+        last_round = r + 1u;
+    }
+    if constexpr (!kInt) {
+        if (packed) {
+            peel_pairs(a, act, it.y, val, oc, oneg, kp, q);
+            return;
+        }
+    }
+    bool push[2] = {false, false};
+    uint32_t ppos[2] = {0u, 0u};
+    if (act) {
+        unsigned long long old[2], inc[2];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const T gx = Val<T>::sign(val, !((oneg >> u) & 1u));  // -g * x
+            if (kInt && packed)
+                inc[u] = ((unsigned long long)(uint32_t)(int32_t)gx << 32) - ((1ull << kp) + it.y);
+            else
+                inc[u] = 0ull - (kOne + it.y);
+            old[u] = atomicAdd(a.cnt + (uint64_t)kCellStride<T> * oc[u], inc[u]);
+            if (!(kInt && packed))
+                Val<T>::atomic_add(a.yw + (uint64_t)kCellStride<T> * oc[u], gx);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const unsigned long long nw = old[u] + inc[u];
+            if (kInt && packed) {
+                const uint32_t low = (uint32_t)nw;
+                push[u] = (low >> kp) == 1u;
+                ppos[u] = low & ((1u << kp) - 1u);
+            } else {
+                push[u] = (nw >> 32) == 1ull;
+                ppos[u] = (uint32_t)nw;
+            }
+        }
+    }
+    lds_push(q, push[0], oc[0], ppos[0]);
+    lds_push(q, push[1], oc[1], ppos[1]);
 }
 
 // Grid-wide barrier in two levels: the workgroups of group g (blockIdx % G)
@@ -1403,7 +1524,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
     if (!skip) {
         const uint32_t nsup = (uint32_t)ctrl->n_support;
         const uint32_t kp = pack_bits(nsup);
-        const bool packed = std::is_same<T, int32_t>::value && a.counted && ctrl->nopack == 0;
+        const bool packed = peel_packed(a, kp);
         if (!a.split0) {
             // round 0's frontier is every cell with exactly one element;
             // packed, each counter also takes its cell's residual in its high
@@ -1416,7 +1537,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 #pragma unroll
                 for (uint32_t m = 0; m < kScanCells; m++) {
                     const uint64_t cidx = base + m * nthreads + gtid;
-                    v[m] = cidx < a.cells ? a.cnt[cidx] : 0ull;
+                    v[m] = cidx < a.cells ? a.cnt[kCellStride<T> * cidx] : 0ull;
                 }
 #pragma unroll
                 for (uint32_t m = 0; m < kScanCells; m++) {
@@ -1444,34 +1565,21 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
             const uint32_t nsweep = (uint32_t)(((uint64_t)(qe - qs) + span - 1u) / span);
             for (uint32_t sw = 0; sw < nsweep; sw++) {
                 const uint64_t i = qs + ((uint64_t)sw * nwaves + gwave) * 64u + lane;
-                bool push[2] = {false, false};
-                uint32_t pcell[2] = {0u, 0u}, ppos[2] = {0u, 0u};
-                if (i < qe) {
-                    // the cell was pure with element pos when queued.  The first
-                    // frontier entry of the element to take its flag recovers it;
-                    // the flag is already set if it was recovered through another
-                    // cell, in this round or an earlier one.  The element and the
-                    // cell's residual are read alongside the claim: once claimed,
-                    // nothing else changes that cell this round.
+                // the cell was pure with element pos when queued.  The first
+                // frontier entry of the element to take its flag recovers it;
+                // the flag is already set if it was recovered through another
+                // cell, in this round or an earlier one.  The element and the
+                // cell's residual are read alongside the claim: once claimed,
+                // nothing else changes that cell this round.
+                uint2 it = make_uint2(0u, 0u);
+                bool have = i < qe;
+                if (have) {
                     const unsigned long long qw =
                         ld_agent64(reinterpret_cast<const unsigned long long*>(a.queue + i));
-                    const uint2 it = make_uint2((uint32_t)qw, (uint32_t)(qw >> 32));
-                    if (it.y < nsup) {
-                        bool done = false;
-                        if constexpr (std::is_same<T, int32_t>::value) {
-                            if (packed) {
-                                peel_entry<T, true>(a, it.x, it.y, kp, r, my_recovered,
-                                                    my_last_round, push, pcell, ppos);
-                                done = true;
-                            }
-                        }
-                        if (!done)
-                            peel_entry<T, false>(a, it.x, it.y, kp, r, my_recovered,
-                                                 my_last_round, push, pcell, ppos);
-                    }
+                    it = make_uint2((uint32_t)qw, (uint32_t)(qw >> 32));
+                    have = it.y < nsup;
                 }
-                lds_push(q, push[0], pcell[0], ppos[0]);
-                lds_push(q, push[1], pcell[1], ppos[1]);
+                peel_step(a, have, it, packed, kp, r, my_recovered, my_last_round, q);
                 flush_pushes(q, false, 2u * kPeelBlock, &sync->tail.v[0], a.queue, a.cells,
                              a.mark, r + 2u);
             }
@@ -1542,7 +1650,7 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
     if (threadIdx.x == 0) q.count = 0;
     lds_barrier();
     const uint32_t kp = pack_bits((uint32_t)ctrl->n_support);
-    const bool packed = std::is_same<T, int32_t>::value && a.counted && ctrl->nopack == 0;
+    const bool packed = peel_packed(a, kp);
     const uint64_t nthreads = (uint64_t)gridDim.x * kBlock;
     const uint64_t gtid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     for (uint64_t base = 0; base < a.cells; base += kScanCells * nthreads) {
@@ -1550,7 +1658,7 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
 #pragma unroll
         for (uint32_t m = 0; m < kScanCells; m++) {
             const uint64_t cidx = base + m * nthreads + gtid;
-            v[m] = cidx < a.cells ? a.cnt[cidx] : 0ull;
+            v[m] = cidx < a.cells ? a.cnt[kCellStride<T> * cidx] : 0ull;
         }
 #pragma unroll
         for (uint32_t m = 0; m < kScanCells; m++) {
@@ -1582,33 +1690,20 @@ __global__ __launch_bounds__(kBlock) void round0_kernel(PeelArgs<T> a) {
     lds_barrier();
     const uint32_t nsup = (uint32_t)ctrl->n_support;
     const uint32_t kp = pack_bits(nsup);
-    const bool packed = std::is_same<T, int32_t>::value && a.counted && ctrl->nopack == 0;
+    const bool packed = peel_packed(a, kp);
     uint32_t qe = a.sync->round0.v[0];
     if (qe > a.cells) qe = a.cells;
     uint32_t my_recovered = 0, my_last_round = 0;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t base = 0; base < qe; base += stride) {
         const uint64_t i = base + (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-        bool push[2] = {false, false};
-        uint32_t pcell[2] = {0u, 0u}, ppos[2] = {0u, 0u};
-        if (i < qe) {
-            const uint2 it = a.queue[i];
-            if (it.y < nsup) {
-                bool done = false;
-                if constexpr (std::is_same<T, int32_t>::value) {
-                    if (packed) {
-                        peel_entry<T, true>(a, it.x, it.y, kp, 0u, my_recovered,
-                                            my_last_round, push, pcell, ppos);
-                        done = true;
-                    }
-                }
-                if (!done)
-                    peel_entry<T, false>(a, it.x, it.y, kp, 0u, my_recovered, my_last_round,
-                                         push, pcell, ppos);
-            }
+        uint2 it = make_uint2(0u, 0u);
+        bool have = i < qe;
+        if (have) {
+            it = a.queue[i];
+            have = it.y < nsup;
         }
-        lds_push(q, push[0], pcell[0], ppos[0]);
-        lds_push(q, push[1], pcell[1], ppos[1]);
+        peel_step(a, have, it, packed, kp, 0u, my_recovered, my_last_round, q);
         flush_pushes(q, false, 2u * kBlock, &a.sync->tail.v[0], a.queue, a.cells, a.mark, 2u);
     }
     flush_pushes(q, true, 0, &a.sync->tail.v[0], a.queue, a.cells, a.mark, 2u);
@@ -1652,7 +1747,8 @@ __global__ __launch_bounds__(kBlock) void leftover_kernel(PeelArgs<T> a) {
 #pragma unroll
         for (int j = 0; j < 3; j++) {
             const uint32_t cell = cell_of(h, j, t, a.c, a.cmask);
-            const T y = packed ? (T)(int32_t)(uint32_t)(a.cnt[cell] >> 32) : a.yw[cell];
+            const T y = packed ? (T)(int32_t)(uint32_t)(a.cnt[cell] >> 32)
+                               : a.yw[(uint64_t)kCellStride<T> * cell];
             e3[j] = Val<T>::sign(y, (h.neg >> j) & 1u);
         }
         a.vals[pos] = median3(e3[0], e3[1], e3[2]);
@@ -1902,7 +1998,8 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     A* vals = reinterpret_cast<A*>(base + L.vals);
     uint8_t* peeled = reinterpret_cast<uint8_t*>(base + L.peeled);
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(base + L.cnt);
-    A* yw = reinterpret_cast<A*>(base + L.yw);
+    // fp32: {counter, residual} records over the two arrays' room
+    A* yw = g.f32 ? reinterpret_cast<A*>(base + L.cnt) + 1 : reinterpret_cast<A*>(base + L.yw);
     uint2* queue = reinterpret_cast<uint2*>(base + L.queue);
     uint32_t* mark = g.f32 ? reinterpret_cast<uint32_t*>(base + L.mark) : nullptr;
     const T* y_agg = static_cast<const T*>(y_agg_v);
@@ -1945,6 +2042,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     sa.c = g.c;
     sa.cmask = g.cmask;
     sa.log2c = g.log2c;
+    sa.cstride = kCellStride<A>;
     sa.vec = bvec;
     hipLaunchKernelGGL(support_kernel, dim3((uint32_t)((L.nchunks + kBlock / 64 - 1) / (kBlock / 64))),
                        dim3(kBlock), 0, s, sa);
@@ -2012,6 +2110,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ca.cmask = g.cmask;
         ca.cells = g.cells;
         ca.last_mask = last_mask;
+        ca.cstride = kCellStride<A>;
         // Rows to spare (two or more per SIMD): one wave per row, its loads in
         // flight together.  Fewer, longer rows (NCF: 1.9 K rows of 1.7 K plan
         // entries) keep more waves busy as a workgroup per row, or, when a

@@ -1,0 +1,46 @@
+"""The fp32 peel on both sides of the support size up to which its counters are
+doubles updated beside their residuals (2^26 elements), and on sketches small
+enough for every launch shape of the peel.
+
+Values are whole numbers below 2^9 in magnitude, so every fp32 and fp64 sum on
+the way is exact and the decode has to return the input bit for bit."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,support,plan", [
+    (1 << 27, 1 << 26, True),         # the largest with doubles
+    (1 << 27, (1 << 26) + 1, True),   # counters and residuals apart
+    (3_000_001, 60_000, True),        # half the CUs
+    (3_000_001, 60_000, False),
+    (40_000_003, 8_000_000, True),    # round 0 over the whole chip
+    (40_000_003, 8_000_000, False),
+])
+def test_fp32_peel_returns_whole_numbers_exactly(n, support, plan):
+    import torch
+    import paper_2402_07529_amd as hc
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n % 1009 + support)
+    x = torch.zeros(n, dtype=torch.float32, device="cuda")
+    if 2 * support > n:  # every other parameter and one more
+        idx = torch.cat([torch.arange(support - 1, device="cuda") * 2,
+                         torch.tensor([1], device="cuda")])
+    else:
+        idx = torch.arange(support, device="cuda") * (n // support)
+    v = torch.randint(1, 512, (support,), device="cuda", generator=gen).float()
+    x[idx] = torch.where(torch.rand(support, device="cuda", generator=gen) < 0.5, -v, v)
+    p = hc.hc_geometry(n, support, 1.5, 1024, 77, "f32")
+    y = torch.empty(p.cells, dtype=torch.float32, device="cuda")
+    b = torch.empty(p.words, dtype=torch.int32, device="cuda")
+    hc.hc_encode(p, x, y, b)
+    out = torch.empty_like(x)
+    info = hc.alloc_info()
+    ws = hc.alloc_workspace(p, support)
+    hc.hc_decode(p, y, b, info, ws, x_out=out, max_support=support,
+                 plan=hc.make_plan(p) if plan else None)
+    inf = hc.read_info(info)
+    assert (inf.success, inf.status, inf.n_support) == (1, 0, support), inf
+    assert torch.equal(out, x)
