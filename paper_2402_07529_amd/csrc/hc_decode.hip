@@ -113,6 +113,7 @@ struct PeelSync {
     SyncLine arrive;  // v[0]: arrivals at the grid barrier, over every barrier of the decode
     SyncLine gen;     // v[0]: barrier generation; v[1]: end of the current frontier
     SyncLine round0;  // v[0]: end of round 0's frontier in the queue
+    SyncLine fill;    // v[0]: chunks of the outputs taken by the filling workgroups
 };
 
 // device mirror of hc_decode_info
@@ -1199,6 +1200,13 @@ struct PeelArgs {  // T: the decode-side arithmetic type
     uint32_t rows, c, cmask, log2c, cells;
     bool counted;   // a counter kernel built the counters (and checked their packing)
     bool split0;    // round 0 ran before the peel kernel, as whole-chip launches
+    // the workgroups from peel_groups on zero the dense outputs while the
+    // others peel: mask_chunks chunks of fill_mask, then fill_x's, fill_chunks in all
+    uint32_t peel_groups;
+    uint32_t mask_chunks, fill_chunks;
+    uint32_t* fill_x;
+    uint32_t* fill_mask;
+    uint64_t x_words, mask_words;
 };
 
 // Round-0 scan of an int32 sketch with a plan: the residual starts as the
@@ -1499,18 +1507,59 @@ __device__ bool grid_barrier(Ctrl* ctrl, PeelSync* sy, uint32_t nblocks, uint32_
     return s_ok != 0;
 }
 
+// ---- zeroing the dense outputs beside the peel -------------------------------------
+//
+// A decode's dense outputs are a pure write stream and the peel is a chain of
+// latencies on part of the CUs.  When the support is sparse (see the launch),
+// workgroups on CUs the peel leaves idle write the zeros while it runs, and
+// the emit then writes only the words that hold members.  Nontemporal stores:
+// plain ones pushed the peel's own lines out of the caches (2^30 parameters,
+// 1.55 M members: decode 1464 us without the overlap, 1202 with plain stores,
+// 945 with nontemporal ones).
+constexpr uint32_t kFillWords = (uint32_t)kChunkBits;  // 128 KiB, the dense output of one emit chunk
+
+__device__ __forceinline__ void fill_zero(uint32_t* __restrict__ p, uint64_t words, uint32_t chunk) {
+    typedef uint32_t V4 __attribute__((ext_vector_type(4)));
+    const V4 zero = {0u, 0u, 0u, 0u};
+    const uint64_t w0 = (uint64_t)chunk * kFillWords;
+    const uint64_t w1 = w0 + kFillWords < words ? w0 + kFillWords : words;
+    const uint64_t v1 = w1 & ~3ull;  // w0 is a multiple of 4 and p 16-byte aligned
+    for (uint64_t w = w0 + 4u * threadIdx.x; w < v1; w += 4u * kPeelBlock)
+        __builtin_nontemporal_store(zero, reinterpret_cast<V4*>(p + w));
+    if (v1 + threadIdx.x < w1) p[v1 + threadIdx.x] = 0u;
+}
+
+template <typename T>
+__device__ void fill_outputs(const PeelArgs<T>& a) {
+    __shared__ uint32_t s_chunk;
+    for (;;) {
+        if (threadIdx.x == 0)
+            s_chunk = add_agent(&a.sync->fill.v[0], 1u);
+        lds_barrier();
+        const uint32_t c = s_chunk;
+        lds_barrier();  // read before it is taken again
+        if (c >= a.fill_chunks) return;
+        if (c < a.mask_chunks) fill_zero(a.fill_mask, a.mask_words, c);
+        else fill_zero(a.fill_x, a.x_words, c - a.mask_chunks);
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
     __shared__ PushBuf<kPeelPushCap> q;
     __shared__ uint32_t s_red[2];
+    if (blockIdx.x >= a.peel_groups) {
+        fill_outputs(a);
+        return;
+    }
     Ctrl* ctrl = a.ctrl;
     PeelSync* sync = a.sync;
     const uint32_t lane = lane_id();
     const uint32_t waves_per_block = kPeelBlock / 64;
     // wave-sized chunks of work go round-robin over the workgroups, so small
     // frontiers still spread over every CU
-    const uint32_t gwave = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
-    const uint32_t nwaves = gridDim.x * waves_per_block;
+    const uint32_t gwave = (threadIdx.x >> 6) * a.peel_groups + blockIdx.x;
+    const uint32_t nwaves = a.peel_groups * waves_per_block;
     const bool skip = ctrl->overflow != 0 || ctrl->bad_plan != 0;
     bool ok = true;
     uint32_t my_recovered = 0, my_last_round = 0;
@@ -1530,7 +1579,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
             // packed, each counter also takes its cell's residual in its high
             // word.  Four cells per lane and pass, loaded together, then staged.
             // 64-bit indexes: a sketch of nearly 2^32 cells must not wrap
-            const uint64_t nthreads = (uint64_t)gridDim.x * kPeelBlock;
+            const uint64_t nthreads = (uint64_t)a.peel_groups * kPeelBlock;
             const uint64_t gtid = (uint64_t)gwave * 64u + lane;
             for (uint64_t base = 0; base < a.cells; base += kScanCells * nthreads) {
                 unsigned long long v[kScanCells];
@@ -1553,7 +1602,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
         // split: round 0 ran before this kernel and the queue holds round 1's
         // frontier after round 0's
         uint32_t fend = 0, gen = 0;
-        ok = grid_barrier(ctrl, sync, gridDim.x, gen++, &fend);
+        ok = grid_barrier(ctrl, sync, a.peel_groups, gen++, &fend);
 
         uint32_t qs = a.split0 ? sync->round0.v[0] : 0u;
         if (qs > a.cells) qs = a.cells;
@@ -1585,7 +1634,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
             }
             flush_pushes(q, true, 0, &sync->tail.v[0], a.queue, a.cells, a.mark, r + 2u);
             qs = qe;
-            ok = grid_barrier(ctrl, sync, gridDim.x, gen++, &fend);
+            ok = grid_barrier(ctrl, sync, a.peel_groups, gen++, &fend);
         }
 
     }
@@ -1606,7 +1655,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         const uint32_t done = __hip_atomic_fetch_add(&ctrl->done, 1u, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1u) {
+        if (done == a.peel_groups - 1u) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             const bool aborted = __hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT) != 0;
@@ -1776,6 +1825,8 @@ struct EmitArgs {  // T: the gradient type; values are kept in Acc<T>
     bool x_vec;     // x_out is 16-byte aligned
     bool mask_vec;  // mask is 16-byte aligned
     bool b_vec;     // b is 16-byte aligned
+    const unsigned int* fill;  // chunks zeroed beside the peel (FILLED)
+    uint32_t mask_chunks;      // of them the mask's, which come first
 };
 
 template <typename T>
@@ -1801,7 +1852,7 @@ __device__ __forceinline__ T estimate_raw(const EmitArgs<T>& a, uint32_t p) {
 // faster here, though plain stores win for a pure write stream).
 constexpr uint32_t kEmitStage = 1024;  // members per LDS window (1/32 of a chunk's parameters)
 
-template <typename T>
+template <typename T, bool FILLED>
 __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
     typedef T V4 __attribute__((ext_vector_type(4)));
     __shared__ uint32_t s_words[kChunkWords];
@@ -1831,6 +1882,55 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
     // another geometry) every member gets the estimate from the aggregate
     const bool raw = a.ctrl->overflow != 0 || a.ctrl->bad_plan != 0;
     const uint64_t chunk_p = chunk * kChunkBits;
+    if (FILLED && chunk + a.mask_chunks < a.fill[0] && total <= kEmitStage) {
+        // zeroed beside the peel: write the words that hold members, two words
+        // at a time per wave, half a wave on each (whole 128-byte lines, so
+        // that no line is read back to be completed)
+        if (total == 0u) return;
+        for (uint32_t i = threadIdx.x; i < total && !raw; i += kBlock) {
+            s_val[i] = (T)a.vals[off + i];
+            s_rec[i] = a.peeled[off + i] != 0u ? 1 : 0;
+        }
+        lds_barrier();
+        const uint32_t half = lane >> 5, bit = lane & 31u;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            uint64_t m = __ballot(w4[k] != 0u);
+            while (m != 0ull) {
+                const uint32_t first = (uint32_t)__ffsll((unsigned long long)m) - 1u;
+                m &= m - 1ull;
+                const bool two = m != 0ull;
+                const uint32_t second = two ? (uint32_t)__ffsll((unsigned long long)m) - 1u : first;
+                m &= m - 1ull;
+                const uint32_t src = half ? second : first;
+                const uint32_t wi = 4u * (wave * 64u + src) + (uint32_t)k;  // word of the chunk
+                const uint32_t word = s_words[wi];
+                const bool mine = half == 0u || two;
+                const uint64_t p = chunk_p + 32ull * wi + bit;
+                const bool member = mine && ((word >> bit) & 1u) != 0u;
+                T v = T(0);
+                bool rec = false;
+                if (member) {
+                    const uint32_t rank = s_pref[wi] + __popc(word & ((1u << bit) - 1u));
+                    if (!raw) {
+                        v = s_val[rank];
+                        rec = s_rec[rank] != 0;
+                    } else {
+                        v = estimate_raw(a, (uint32_t)p);
+                    }
+                    if (a.coo_idx != nullptr && off + rank < a.coo_cap) {
+                        a.coo_idx[off + rank] = (uint32_t)p;
+                        a.coo_val[off + rank] = v;
+                    }
+                }
+                if (mine && p < a.n) a.x_out[p] = v;
+                const uint64_t recs = __ballot(rec);
+                if (a.mask != nullptr && mine && bit == 0u && chunk * kChunkWords + wi < a.words)
+                    a.mask[chunk * kChunkWords + wi] = (uint32_t)(half ? recs >> 32 : recs);
+            }
+        }
+        return;
+    }
     // the members' values and flags go through LDS in windows of kEmitStage
     // consecutive ranks, [wlo, whi) of the chunk's; an iteration (1024
     // parameters) holds at most 1024 members, so a window that starts at its
@@ -2206,9 +2306,30 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         hipLaunchKernelGGL(round0_kernel<A>, dim3(grid0), dim3(kBlock), 0, s, pa);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    const bool x_vec = (reinterpret_cast<uintptr_t>(out.x_out) & 15u) == 0;
+    const bool mask_vec = (reinterpret_cast<uintptr_t>(out.mask) & 15u) == 0;
+    // Zero the dense outputs beside the peel when at least 64 parameters go on
+    // one support element (by the support bound): the emit then writes few of
+    // the lines again.  Measured at 2^27 parameters (decode without and with):
+    // 0.2 % dense 593 and 521 us, 1 % 602 and 583, 3 % 940 and 947, 7 % 1586
+    // and 1614; rows of 64 at 2^26 and 1 % 310 and 267.  A quarter of the CUs
+    // writes at the full rate (48 of 256 workgroups 1124 us on the 2^30 case,
+    // 64 945, 96 939, 128 959; the smaller cases are best at 24 to 64).
+    uint32_t fill_groups = 0;
+    if (out.x_out != nullptr && x_vec && mask_vec && L.cap <= g.n / 64) {
+        fill_groups = (uint32_t)di.cus - peel_grid;
+        if (fill_groups > (uint32_t)di.cus / 4u) fill_groups = (uint32_t)di.cus / 4u;
+    }
+    pa.peel_groups = peel_grid;
+    pa.fill_x = static_cast<uint32_t*>(out.x_out);
+    pa.fill_mask = out.mask;
+    pa.x_words = g.n;
+    pa.mask_words = out.mask != nullptr ? g.words : 0;
+    pa.mask_chunks = (uint32_t)((pa.mask_words + kFillWords - 1) / kFillWords);
+    pa.fill_chunks = pa.mask_chunks + (uint32_t)((pa.x_words + kFillWords - 1) / kFillWords);
     void* args[] = {&pa};
     e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&peel_kernel<A>),
-                                   dim3(peel_grid), dim3(kPeelBlock), args,
+                                   dim3(peel_grid + fill_groups), dim3(kPeelBlock), args,
                                    0, s);
     if (e != hipSuccess) return e;
 
@@ -2237,10 +2358,15 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ea.cmask = g.cmask;
         ea.log2c = g.log2c;
         ea.last_mask = last_mask;
-        ea.x_vec = (reinterpret_cast<uintptr_t>(out.x_out) & 15u) == 0;
-        ea.mask_vec = (reinterpret_cast<uintptr_t>(out.mask) & 15u) == 0;
+        ea.x_vec = x_vec;
+        ea.mask_vec = mask_vec;
+        ea.fill = fill_groups != 0 ? &sync->fill.v[0] : nullptr;
+        ea.mask_chunks = pa.mask_chunks;
         ea.b_vec = bvec;
-        hipLaunchKernelGGL(emit_kernel<T>, dim3((uint32_t)L.nchunks), dim3(kBlock), 0, s, ea);
+        if (fill_groups != 0)
+            hipLaunchKernelGGL((emit_kernel<T, true>), dim3((uint32_t)L.nchunks), dim3(kBlock), 0, s, ea);
+        else
+            hipLaunchKernelGGL((emit_kernel<T, false>), dim3((uint32_t)L.nchunks), dim3(kBlock), 0, s, ea);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
