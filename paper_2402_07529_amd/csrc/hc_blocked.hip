@@ -137,21 +137,6 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* s_tmp) {
     return t;
 }
 
-// Position of the r-th (0-based) set bit of w; r < popcount(w).
-__device__ __forceinline__ uint32_t select_bit(uint32_t w, uint32_t r) {
-    uint32_t pos = 0;
-#pragma unroll
-    for (uint32_t width = 16; width >= 1; width >>= 1) {
-        const uint32_t c = __popc(w & ((1u << width) - 1u));
-        if (r >= c) {
-            r -= c;
-            w >>= width;
-            pos += width;
-        }
-    }
-    return pos;
-}
-
 __device__ __forceinline__ uint32_t load_bword(const uint32_t* b, uint64_t k, uint64_t words,
                                                uint32_t last_mask) {
     if (k >= words) return 0u;
@@ -401,40 +386,6 @@ __device__ __forceinline__ Member member_of(const uint32_t* s_tab, uint32_t bl, 
     const uint32_t ej = m.j == 0 ? m.e[0] : (m.j == 1 ? m.e[1] : m.e[2]);
     m.t = ((i & cmask) - ((ej >> 16) & 0x3ffu)) & cmask;
     return m;
-}
-
-// Hands the set bits of the lanes' words (one word per lane) out to the
-// lanes in order, 64 at a time: f(s, valid, owner, bit) is called by every
-// lane of the wave with s = the rank of its bit among all set bits, owner =
-// the lane holding it and bit its position (valid = s < total).  Returns the
-// number of set bits.  Consecutive lanes get consecutive bits, so the LDS
-// accesses of one call hit nearby columns.
-template <typename F>
-__device__ __forceinline__ uint32_t for_each_set_bit(uint32_t word, F&& f) {
-    // exclusive prefix of the lanes' popcounts (0..32, six bits) from one
-    // ballot per bit: no cross-lane data movement through LDS
-    const uint32_t lane = lane_id();
-    const uint32_t cw = __popc(word);
-    uint32_t excl = 0, total = 0;
-#pragma unroll
-    for (int b = 0; b < 6; b++) {
-        const uint64_t m = __ballot((cw >> b) & 1u);
-        excl += lanes_below(m) << b;
-        total += (uint32_t)__popcll(m) << b;
-    }
-    for (uint32_t s0 = 0; s0 < total; s0 += 64) {
-        const uint32_t s = s0 + lane;
-        uint32_t lo = 0;
-#pragma unroll
-        for (uint32_t step = 32; step >= 1; step >>= 1) {
-            const uint32_t cand = lo + step;
-            if ((uint32_t)__shfl(excl, (int)cand) <= s) lo = cand;
-        }
-        const uint32_t wrd = (uint32_t)__shfl(word, (int)lo);
-        const uint32_t r = s - (uint32_t)__shfl(excl, (int)lo);
-        f(s, s < total, lo, select_bit(wrd, r));
-    }
-    return total;
 }
 
 // WHOLE: a global sketch small enough for one workgroup's LDS is decoded as a

@@ -42,6 +42,7 @@
 //            from the residual sketch (Algorithm 1, last recovery step), on
 //            the whole chip: when decoding fails most of the support is left;
 //   emit     dense output, recovered mask and COO from E and the values.
+#include <algorithm>
 #include <type_traits>
 
 #include "hc_device.h"
@@ -56,6 +57,7 @@ constexpr int kPeelBlock = 1024;  // lanes per workgroup of the persistent peel 
 constexpr uint32_t kScanCells = 4;  // cells a lane takes per pass of the round-0 scan
 constexpr uint32_t kPeelPushCap = 8 * kPeelBlock;  // staged frontier entries per workgroup (64 KiB)
 constexpr uint64_t kPeelHalfGridCells = 8ull << 20;  // below this many cells the peel uses half the CUs
+constexpr uint64_t kPeelMostGridCellsF32 = 2ull << 20;  // fp32: three quarters from here to that bound
 constexpr uint64_t kPeelHalfGridCellsInt = 32ull << 20;  // the same with residuals in the counters
 constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a packed counter
 
@@ -81,6 +83,12 @@ __device__ __forceinline__ uint32_t pack_bits(uint64_t nsup) {
 }
 __device__ __forceinline__ bool fits_packed(unsigned long long acc, uint32_t k) {
     return ((acc >> 32) << k) + (acc & 0xffffffffull) < (1ull << 32);
+}
+// The same for one of `parts` addends of a counter: if each fits its share,
+// their sum fits.
+__device__ __forceinline__ bool fits_packed_share(unsigned long long acc, uint32_t k,
+                                                  uint32_t parts) {
+    return (((acc >> 32) << k) + (acc & 0xffffffffull)) * parts < (1ull << 32);
 }
 constexpr uint64_t kChunkBits = (uint64_t)kChunkWords * 32;
 constexpr uint64_t kBarrierTimeoutTicks = 500000000ull;  // 5 s at the 100 MHz real-time clock
@@ -127,11 +135,35 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
+// Initial residuals, counters and marks of cells first, first + step, ...
+// zero_cnt: the counters are built by atomics (without a plan, or from parts
+// of rows); with a plan a row's counters are otherwise stored whole.
+// int32 with a plan: the round-0 scan takes the residual from the aggregate
+// itself (into the counters' high words, or into yw when they do not pack).
+template <typename T>
+__device__ __forceinline__ void prep_cells(const T* __restrict__ y_agg,
+                                           typename Acc<T>::type* __restrict__ yw,
+                                           unsigned long long* __restrict__ cnt, uint32_t cells,
+                                           bool planned, bool zero_cnt,
+                                           uint32_t* __restrict__ mark, uint64_t first,
+                                           uint64_t step) {
+    for (uint64_t i = first; i < cells; i += step) {
+        if constexpr (std::is_same<T, float>::value) {
+            // one 16-byte store per record
+            reinterpret_cast<double2*>(cnt)[i] = make_double2(0.0, (double)y_agg[i]);
+            mark[i] = 0u;
+        } else {
+            if (!planned) yw[i] = y_agg[i];
+            if (zero_cnt) cnt[i] = 0ull;
+        }
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void prep_kernel(const T* __restrict__ y_agg,
                                                       typename Acc<T>::type* __restrict__ yw,
                                                       unsigned long long* __restrict__ cnt,
-                                                      uint32_t cells, bool planned,
+                                                      uint32_t cells, bool planned, bool zero_cnt,
                                                       Ctrl* __restrict__ ctrl,
                                                       PeelSync* __restrict__ sync,
                                                       uint32_t* __restrict__ mark) {
@@ -140,22 +172,8 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(const T* __restrict__ y_ag
         for (uint32_t k = threadIdx.x; k < sizeof(PeelSync) / 4; k += kBlock)
             reinterpret_cast<uint32_t*>(sync)[k] = 0u;
     }
-    const uint64_t step = (uint64_t)gridDim.x * kBlock;
-    // int32 with a plan: the round-0 scan takes the residual from the
-    // aggregate itself (into the counters' high words, or into yw when they
-    // do not pack)
-    const bool copy = !(std::is_same<T, int32_t>::value && planned);
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < cells; i += step) {
-        if constexpr (std::is_same<T, float>::value) {
-            // one 16-byte store per record (with a plan the counter kernel
-            // overwrites the counter)
-            reinterpret_cast<double2*>(cnt)[i] = make_double2(0.0, (double)y_agg[i]);
-            mark[i] = 0u;
-        } else {
-            if (copy) yw[i] = (typename Acc<T>::type)y_agg[i];
-            if (!planned) cnt[i] = 0ull;
-        }
-    }
+    prep_cells<T>(y_agg, yw, cnt, cells, planned, zero_cnt, mark,
+                  (uint64_t)blockIdx.x * kBlock + threadIdx.x, (uint64_t)gridDim.x * kBlock);
 }
 
 // Bitmap word k, with bits at or past n cleared in the last word.
@@ -431,6 +449,71 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
     if (chunk + 1 == a.nchunks && lane == 0 && a.woffb != nullptr) a.woffb[a.nb] = base;
 }
 
+// The count, scan, support and (with a plan) prep steps of a short bitmap in
+// one launch: every chunk's workgroup sums the popcounts of all words before
+// it by itself (at most 2^19 bytes, from the caches), a thread per word then
+// ranks its own, and the last chunk's writes the control block.  Workgroups
+// past the chunks prepare the cells.  Four launches cost about 28 us at 2^21
+// parameters, nearly all latency.
+// On 61 chunks (2 M parameters, 5 % dense, int32, 45 rounds) the decode went 313 -> 266 us
+// with this, split rows and shared emit chunks.
+constexpr uint64_t kSmallChunks = 128;
+constexpr uint32_t kSupportBlock = kChunkWords;
+
+template <typename T>
+__global__ __launch_bounds__(kSupportBlock) void support_small_kernel(
+    SupportArgs a, PeelSync* __restrict__ sync, const T* __restrict__ y_agg,
+    typename Acc<T>::type* __restrict__ yw, uint32_t cells, bool zero_cnt,
+    uint32_t* __restrict__ mark) {
+    __shared__ uint32_t s_tmp[kSupportBlock / 64];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t nchunks = (uint32_t)a.nchunks;
+    if (blockIdx.x >= nchunks) {
+        prep_cells<T>(y_agg, yw, a.cnt, cells, true, zero_cnt, mark,
+                      (uint64_t)(blockIdx.x - nchunks) * kSupportBlock + tid,
+                      (uint64_t)(gridDim.x - nchunks) * kSupportBlock);
+        return;
+    }
+    const uint32_t c0 = blockIdx.x * kChunkWords;
+    const uint32_t w = c0 + tid;
+    const uint32_t word = load_word_nb(a.b, w, a.words, a.last_mask);
+    // the words before the chunk are whole (c0 < words)
+    uint32_t sum = 0;
+    if (a.vec) {
+#pragma unroll 8
+        for (uint32_t i = tid; i < c0 / 4; i += kSupportBlock) {
+            const uint4 v = reinterpret_cast<const uint4*>(a.b)[i];
+            sum += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        }
+    } else {
+#pragma unroll 8
+        for (uint32_t i = tid; i < c0; i += kSupportBlock) sum += __popc(a.b[i]);
+    }
+    uint32_t base, total;
+    block_exclusive_scan(sum, s_tmp, &base);
+    const uint32_t excl = block_exclusive_scan(__popc(word), s_tmp, &total);
+    if (tid == 0) a.blk[blockIdx.x] = base;
+    if (a.woffb != nullptr && w < a.words && (w & ((1u << a.log2wpb) - 1u)) == 0u)
+        a.woffb[w >> a.log2wpb] = base + excl;
+    const uint32_t wave = uniform(tid >> 6);
+    const uint32_t wbase = base + uniform(excl);  // lane 0's rank: the wave's first
+    for_each_set_bit(word, [&](uint32_t s, bool valid, uint32_t owner, uint32_t bit) {
+        if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit);
+    });
+    if (blockIdx.x == nchunks - 1u) {
+        if (tid < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(a.ctrl)[tid] = 0u;
+        if (tid < sizeof(PeelSync) / 4) reinterpret_cast<uint32_t*>(sync)[tid] = 0u;
+        lds_barrier();
+        __builtin_amdgcn_s_waitcnt(0);
+        if (tid == 0) {
+            const uint32_t all = base + total;
+            if (a.woffb != nullptr) a.woffb[a.nb] = all;
+            a.ctrl->n_support = all;
+            a.ctrl->overflow = (uint64_t)all > a.cap ? 1u : 0u;
+        }
+    }
+}
+
 // Coherent (agent-scope) 64-bit loads and stores: the peel's grid barrier
 // only orders a workgroup's memory operations (it waits for them to complete)
 // and does not write back or invalidate the L2, so every value one workgroup
@@ -536,9 +619,11 @@ struct CounterArgs {
     uint64_t n, seed, words, nb;
     uint32_t rows, c, cmask, cells, last_mask;
     uint32_t cstride;  // 64-bit words from one counter to the next
+    uint32_t split;    // counter_kernel: workgroups sharing a row's entries
 };
 
-// One workgroup per sketch row (grid-stride).  Cell k of row r gathers, from
+// One workgroup per sketch row (grid-stride), or `split` workgroups per row,
+// each taking a run of its plan entries.  Cell k of row r gathers, from
 // every (batch b, hash j) in the row's plan entry list, the parameter
 // t = (k - bias_j(b)) mod c of batch b: if its bit is set it adds 2^32 + its
 // rank in the support.  Integer sums, so the result equals the atomic build
@@ -556,6 +641,7 @@ struct CounterArgs {
 // kernel's scan: queuing them here took one append on the shared queue tail
 // per row (VGG19: 10 K rows, about 0.15 ms of contended atomics).
 constexpr uint32_t kStage = 64;  // live batches staged in LDS at a time
+constexpr uint64_t kSplitEntries = 32;    // plan entries a part of a split row has at least, on average
 constexpr uint64_t kWaveRowsEntries = 8;  // plan entries per row up to which a wave takes a row
 
 template <int C>
@@ -568,20 +654,28 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
     __shared__ uint32_t s_boff[kStage];
     __shared__ uint2 s_live[kBlock];
     __shared__ uint32_t s_tmp[kWaves];
-    const PlanHeader* hdr = a.hdr;
-    const bool ok = hdr->magic == kPlanMagic && hdr->n == a.n && hdr->seed == a.seed &&
-                    hdr->c == a.c && hdr->rows == a.rows;
-    if (!ok) {
+    // loaded together with the first row's bounds: tested one after the other,
+    // each of the three costs a memory latency before the row begins
+    const PlanHeader hdr = *a.hdr;
+    const uint32_t overflow = a.ctrl->overflow;
+    const unsigned long long nsup = a.ctrl->n_support;
+    const uint32_t lane = lane_id();
+    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t nparts = a.rows * a.split;
+    uint32_t part = blockIdx.x;  // < nparts: the grid has at most that many
+    uint32_t row = part / a.split;
+    uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
+    if (!(hdr.magic == kPlanMagic && hdr.n == a.n && hdr.seed == a.seed && hdr.c == a.c &&
+          hdr.rows == a.rows)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) a.ctrl->bad_plan = 1u;
         return;
     }
-    if (a.ctrl->overflow) return;
-    const uint32_t kpack = pack_bits(a.ctrl->n_support);
-    const uint32_t lane = lane_id();
-    const uint32_t wave = threadIdx.x >> 6;
-    for (uint32_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    if (overflow) return;
+    const uint32_t kpack = pack_bits(nsup);
+    for (;;) {
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) s_acc[k] = 0ull;
-        const uint32_t e0 = a.rowoff[row], e1 = a.rowoff[row + 1];
+        const uint32_t len = (r1 - r0 + a.split - 1u) / a.split;
+        const uint32_t e0 = min(r0 + (part - row * a.split) * len, r1), e1 = min(e0 + len, r1);
         for (uint32_t base = e0; base < e1; base += kBlock) {
             // screen
             const uint32_t e = base + threadIdx.x;
@@ -630,14 +724,24 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
                 lds_barrier();  // the staging buffers are reused
             }
         }
+        // a whole row is stored; the parts of a split row are added, each
+        // within its share of the packed form's range
+        lds_barrier();
         bool fits = true;
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) {
             const unsigned long long acc = s_acc[k];
-            a.cnt[(uint64_t)a.cstride * (row * C + k)] = acc;
-            fits = fits && fits_packed(acc, kpack);
+            unsigned long long* const dst = a.cnt + (uint64_t)a.cstride * (row * C + k);
+            if (a.split == 1u) *dst = acc;
+            else if (acc != 0ull) atomicAdd(dst, acc);
+            fits = fits && fits_packed_share(acc, kpack, a.split);
         }
         flag_unpackable(a.ctrl, fits);
-        lds_barrier();  // s_acc is cleared for the next row
+        part += gridDim.x;
+        if (part >= nparts) return;
+        lds_barrier();  // s_acc is cleared for the next part
+        row = part / a.split;
+        r0 = a.rowoff[row];
+        r1 = a.rowoff[row + 1];
     }
 }
 
@@ -1367,6 +1471,41 @@ __device__ __forceinline__ void peel_pairs(const PeelArgs<double>& a, bool act, 
     }
 }
 
+// An entry whose element it recovers (peel_decide), with separate atomics per
+// cell: sets the (at most two) cells that became pure, with their elements.
+template <typename T, bool PACKED>
+__device__ __forceinline__ bool peel_entry(const PeelArgs<T>& a, uint2 it, uint32_t kp, uint32_t r,
+                                           bool (&push)[2], uint32_t (&oc)[2],
+                                           uint32_t (&ppos)[2]) {
+    T val;
+    uint32_t oneg;
+    if (!peel_decide<T, PACKED>(a, it.x, it.y, r, val, oc, oneg)) return false;
+    unsigned long long old[2], inc[2];
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const T gx = Val<T>::sign(val, !((oneg >> u) & 1u));  // -g * x
+        if (PACKED)
+            inc[u] = ((unsigned long long)(uint32_t)(int32_t)gx << 32) - ((1ull << kp) + it.y);
+        else
+            inc[u] = 0ull - (kOne + it.y);
+        old[u] = atomicAdd(a.cnt + (uint64_t)kCellStride<T> * oc[u], inc[u]);
+        if (!PACKED) Val<T>::atomic_add(a.yw + (uint64_t)kCellStride<T> * oc[u], gx);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const unsigned long long nw = old[u] + inc[u];
+        if (PACKED) {
+            const uint32_t low = (uint32_t)nw;
+            push[u] = (low >> kp) == 1u;
+            ppos[u] = low & ((1u << kp) - 1u);
+        } else {
+            push[u] = (nw >> 32) == 1ull;
+            ppos[u] = (uint32_t)nw;
+        }
+    }
+    return true;
+}
+
 // One frontier entry per lane (have), taken by every lane of the wave: the
 // entry's element is recovered if it is the one to do so, leaves its two other
 // cells, and those that became pure are staged for the next frontier.
@@ -1374,53 +1513,24 @@ template <typename T, typename Q>
 __device__ __forceinline__ void peel_step(const PeelArgs<T>& a, bool have, uint2 it, bool packed,
                                           uint32_t kp, uint32_t r, uint32_t& recovered,
                                           uint32_t& last_round, Q& q) {
-    T val = T(0);
-    uint32_t oc[2] = {0u, 0u}, oneg = 0;
+    uint32_t oc[2] = {0u, 0u}, ppos[2] = {0u, 0u};
+    bool push[2] = {false, false};
     bool act = false;
-    constexpr bool kInt = std::is_same<T, int32_t>::value;
-    if (have) {
-        if (kInt && packed)
-            act = peel_decide<T, kInt>(a, it.x, it.y, r, val, oc, oneg);
-        else
-            act = peel_decide<T, false>(a, it.x, it.y, r, val, oc, oneg);
+    if constexpr (std::is_same<T, int32_t>::value) {
+        if (have)
+            act = packed ? peel_entry<T, true>(a, it, kp, r, push, oc, ppos)
+                         : peel_entry<T, false>(a, it, kp, r, push, oc, ppos);
+    } else if (packed) {
+        T val = T(0);
+        uint32_t oneg = 0;
+        if (have) act = peel_decide<T, false>(a, it.x, it.y, r, val, oc, oneg);
+        peel_pairs(a, act, it.y, val, oc, oneg, kp, q);
+    } else if (have) {
+        act = peel_entry<T, false>(a, it, kp, r, push, oc, ppos);
     }
     if (act) {
         recovered++;
         last_round = r + 1u;
-    }
-    if constexpr (!kInt) {
-        if (packed) {
-            peel_pairs(a, act, it.y, val, oc, oneg, kp, q);
-            return;
-        }
-    }
-    bool push[2] = {false, false};
-    uint32_t ppos[2] = {0u, 0u};
-    if (act) {
-        unsigned long long old[2], inc[2];
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            const T gx = Val<T>::sign(val, !((oneg >> u) & 1u));  // -g * x
-            if (kInt && packed)
-                inc[u] = ((unsigned long long)(uint32_t)(int32_t)gx << 32) - ((1ull << kp) + it.y);
-            else
-                inc[u] = 0ull - (kOne + it.y);
-            old[u] = atomicAdd(a.cnt + (uint64_t)kCellStride<T> * oc[u], inc[u]);
-            if (!(kInt && packed))
-                Val<T>::atomic_add(a.yw + (uint64_t)kCellStride<T> * oc[u], gx);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-            const unsigned long long nw = old[u] + inc[u];
-            if (kInt && packed) {
-                const uint32_t low = (uint32_t)nw;
-                push[u] = (low >> kp) == 1u;
-                ppos[u] = low & ((1u << kp) - 1u);
-            } else {
-                push[u] = (nw >> 32) == 1ull;
-                ppos[u] = (uint32_t)nw;
-            }
-        }
     }
     lds_push(q, push[0], oc[0], ppos[0]);
     lds_push(q, push[1], oc[1], ppos[1]);
@@ -1552,14 +1662,15 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
         fill_outputs(a);
         return;
     }
+    const uint32_t groups = a.peel_groups;
     Ctrl* ctrl = a.ctrl;
     PeelSync* sync = a.sync;
     const uint32_t lane = lane_id();
     const uint32_t waves_per_block = kPeelBlock / 64;
     // wave-sized chunks of work go round-robin over the workgroups, so small
     // frontiers still spread over every CU
-    const uint32_t gwave = (threadIdx.x >> 6) * a.peel_groups + blockIdx.x;
-    const uint32_t nwaves = a.peel_groups * waves_per_block;
+    const uint32_t gwave = (threadIdx.x >> 6) * groups + blockIdx.x;
+    const uint32_t nwaves = groups * waves_per_block;
     const bool skip = ctrl->overflow != 0 || ctrl->bad_plan != 0;
     bool ok = true;
     uint32_t my_recovered = 0, my_last_round = 0;
@@ -1579,7 +1690,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
             // packed, each counter also takes its cell's residual in its high
             // word.  Four cells per lane and pass, loaded together, then staged.
             // 64-bit indexes: a sketch of nearly 2^32 cells must not wrap
-            const uint64_t nthreads = (uint64_t)a.peel_groups * kPeelBlock;
+            const uint64_t nthreads = (uint64_t)groups * kPeelBlock;
             const uint64_t gtid = (uint64_t)gwave * 64u + lane;
             for (uint64_t base = 0; base < a.cells; base += kScanCells * nthreads) {
                 unsigned long long v[kScanCells];
@@ -1602,7 +1713,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
         // split: round 0 ran before this kernel and the queue holds round 1's
         // frontier after round 0's
         uint32_t fend = 0, gen = 0;
-        ok = grid_barrier(ctrl, sync, a.peel_groups, gen++, &fend);
+        ok = grid_barrier(ctrl, sync, groups, gen++, &fend);
 
         uint32_t qs = a.split0 ? sync->round0.v[0] : 0u;
         if (qs > a.cells) qs = a.cells;
@@ -1634,7 +1745,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
             }
             flush_pushes(q, true, 0, &sync->tail.v[0], a.queue, a.cells, a.mark, r + 2u);
             qs = qe;
-            ok = grid_barrier(ctrl, sync, a.peel_groups, gen++, &fend);
+            ok = grid_barrier(ctrl, sync, groups, gen++, &fend);
         }
 
     }
@@ -1655,7 +1766,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         const uint32_t done = __hip_atomic_fetch_add(&ctrl->done, 1u, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
-        if (done == a.peel_groups - 1u) {
+        if (done == groups - 1u) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             const bool aborted = __hip_atomic_load(&ctrl->abort, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT) != 0;
@@ -1822,6 +1933,7 @@ struct EmitArgs {  // T: the gradient type; values are kept in Acc<T>
     uint32_t* mask;
     uint64_t n, words, seed;
     uint32_t rows, c, cmask, log2c, last_mask;
+    uint32_t log2parts;  // workgroups per chunk
     bool x_vec;     // x_out is 16-byte aligned
     bool mask_vec;  // mask is 16-byte aligned
     bool b_vec;     // b is 16-byte aligned
@@ -1849,7 +1961,9 @@ __device__ __forceinline__ T estimate_raw(const EmitArgs<T>& a, uint32_t p) {
 // eight workgroups per CU) against 2048 (22 KB, seven) took NCF's decode from
 // 1.422 to 1.413 ms with VGG19's and LSTM's unchanged, and 4096 cost NCF
 // 44 us.  The dense output goes out with nontemporal stores (measured 1-2 %
-// faster here, though plain stores win for a pure write stream).
+// faster here, though plain stores win for a pure write stream).  A short
+// bitmap's chunks are shared by 2^log2parts workgroups, each taking a run of
+// the chunk's iterations, so that its outputs use the whole chip.
 constexpr uint32_t kEmitStage = 1024;  // members per LDS window (1/32 of a chunk's parameters)
 
 template <typename T, bool FILLED>
@@ -1863,9 +1977,14 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
     __shared__ uint8_t s_rec[kEmitStage];
     const uint32_t lane = lane_id();
     const uint32_t wave = threadIdx.x >> 6;
-    const uint64_t chunk = blockIdx.x;
+    const uint64_t chunk = blockIdx.x >> a.log2parts;
+    const uint32_t part = blockIdx.x & ((1u << a.log2parts) - 1u);
     const uint64_t w0 = chunk * kChunkWords + 4ull * threadIdx.x;
     const uint4 wv = load_words4(a.b, w0, a.words, a.last_mask, a.b_vec);
+    const uint64_t off = a.blk[chunk];
+    // with no valid element list (support over capacity, or a plan for
+    // another geometry) every member gets the estimate from the aggregate
+    const bool raw = (a.ctrl->overflow | a.ctrl->bad_plan) != 0;
     const uint32_t w4[4] = {wv.x, wv.y, wv.z, wv.w};
     const uint32_t mine = __popc(wv.x) + __popc(wv.y) + __popc(wv.z) + __popc(wv.w);
     uint32_t total;
@@ -1877,16 +1996,12 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
         run += __popc(w4[k]);
     }
     lds_barrier();
-    const uint64_t off = a.blk[chunk];
-    // with no valid element list (support over capacity, or a plan for
-    // another geometry) every member gets the estimate from the aggregate
-    const bool raw = a.ctrl->overflow != 0 || a.ctrl->bad_plan != 0;
     const uint64_t chunk_p = chunk * kChunkBits;
     if (FILLED && chunk + a.mask_chunks < a.fill[0] && total <= kEmitStage) {
         // zeroed beside the peel: write the words that hold members, two words
         // at a time per wave, half a wave on each (whole 128-byte lines, so
         // that no line is read back to be completed)
-        if (total == 0u) return;
+        if (total == 0u || part != 0u) return;
         for (uint32_t i = threadIdx.x; i < total && !raw; i += kBlock) {
             s_val[i] = (T)a.vals[off + i];
             s_rec[i] = a.peeled[off + i] != 0u ? 1 : 0;
@@ -1935,9 +2050,11 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
     // consecutive ranks, [wlo, whi) of the chunk's; an iteration (1024
     // parameters) holds at most 1024 members, so a window that starts at its
     // first member covers it.  wlo, whi and the reload test are uniform.
-    uint32_t wlo = 0, whi = 0;
     constexpr uint32_t kIterWords = 4 * kBlock / 32;  // bitmap words per iteration
-    for (uint32_t it = 0; it < kChunkBits / (4 * kBlock); it++) {
+    const uint32_t iters = (uint32_t)(kChunkBits / (4 * kBlock)) >> a.log2parts;
+    const uint32_t it0 = part * iters;
+    uint32_t wlo = s_pref[it0 * kIterWords], whi = wlo;
+    for (uint32_t it = it0; it < it0 + iters; it++) {
         if (!raw) {
             const uint32_t wf = it * kIterWords, wl = wf + kIterWords - 1;
             const uint32_t r1 = s_pref[wl] + __popc(s_words[wl]);  // past the iteration's last
@@ -2023,6 +2140,7 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
         // wave and iteration
         lds_barrier();
         const uint64_t mw0 = chunk * kChunkWords + 4ull * threadIdx.x;
+        if (threadIdx.x * 4u / kIterWords / iters != part) return;  // another part's words
         if (a.mask_vec && mw0 + 4 <= a.words) {
             *reinterpret_cast<uint4*>(a.mask + mw0) =
                 make_uint4(s_mask[4 * threadIdx.x], s_mask[4 * threadIdx.x + 1],
@@ -2109,18 +2227,25 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     hipError_t e = device_info(&di);
     if (e != hipSuccess) return e;
 
-    uint64_t grid = ((uint64_t)g.cells + kBlock - 1) / kBlock;
-    if (grid > (uint64_t)di.cus * 16) grid = (uint64_t)di.cus * 16;
-    hipLaunchKernelGGL(prep_kernel<T>, dim3((uint32_t)grid), dim3(kBlock), 0, s, y_agg, yw, cnt,
-                       g.cells, planned, ctrl, sync, mark);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     const uint32_t last_mask = (g.n & 31u) ? ((1u << (g.n & 31u)) - 1u) : 0xffffffffu;
     const bool bvec = (reinterpret_cast<uintptr_t>(b) & 15u) == 0;
-    hipLaunchKernelGGL(tile_count_kernel, dim3((uint32_t)L.ntiles), dim3(kBlock), 0, s, b,
-                       g.words, last_mask, bvec, L.nchunks, cpre, tcnt);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, tcnt, L.ntiles, ctrl, L.cap);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const uint64_t nb = (g.n + g.c - 1) / g.c;
+    // A wave per row when rows are to spare (two or more per SIMD), a wave per
+    // row too when a row has only a few entries, else workgroups per row: one,
+    // or several sharing a row's entries when rows are too few to fill the chip
+    // and long enough to share.
+    const bool wave_rows = planned && (uint64_t)g.rows >= 8ull * (uint64_t)di.cus;
+    const bool few_entries = 3ull * nb <= kWaveRowsEntries * g.rows;
+    uint32_t split = 1;
+    if (planned && !wave_rows && !few_entries)
+        while (split < 64 && (uint64_t)g.rows * split < 4ull * (uint64_t)di.cus &&
+               3ull * nb >= (uint64_t)g.rows * split * kSplitEntries)
+            split *= 2;
+    // (2^21 parameters, 0.2 % dense: 6 rows of 1024 entries, decode 349 -> 109
+    // us with the shorter support steps; BERT-base at 0.26 %, 345 rows: the
+    // counters took 260 us on 1.3 workgroups per CU)
+    const bool zero_cnt = !planned || split > 1;
+    const uint64_t cell_groups = ((uint64_t)g.cells + kBlock - 1) / kBlock;
     SupportArgs sa;
     sa.b = b;
     sa.cpre = cpre;
@@ -2137,22 +2262,47 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     sa.seed = g.seed;
     sa.last_mask = last_mask;
     sa.log2wpb = planned ? g.log2c - 5u : 0u;  // planned sketches have c >= 256
-    sa.nb = (uint32_t)((g.n + g.c - 1) / g.c);
+    sa.nb = (uint32_t)nb;
     sa.rows = g.rows;
     sa.c = g.c;
     sa.cmask = g.cmask;
     sa.log2c = g.log2c;
     sa.cstride = kCellStride<A>;
     sa.vec = bvec;
-    hipLaunchKernelGGL(support_kernel, dim3((uint32_t)((L.nchunks + kBlock / 64 - 1) / (kBlock / 64))),
-                       dim3(kBlock), 0, s, sa);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // the support offsets and lists, and the cells' initial state
+    const bool small = L.nchunks <= kSmallChunks;
+    if (!planned || !small) {
+        const uint64_t cap = (uint64_t)di.cus * 16;
+        const uint32_t grid = (uint32_t)(cell_groups < cap ? cell_groups : cap);
+        hipLaunchKernelGGL(prep_kernel<T>, dim3(grid), dim3(kBlock), 0, s, y_agg, yw, cnt,
+                           g.cells, planned, zero_cnt, ctrl, sync, mark);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (small) {
+        // the cells' preparation rides along where nothing in this launch needs it
+        uint32_t extra = 0;
+        if (planned && (g.f32 || zero_cnt))
+            extra = (uint32_t)std::min<uint64_t>((g.cells + kSupportBlock - 1) / kSupportBlock,
+                                                 (uint64_t)di.cus * 2);
+        hipLaunchKernelGGL(support_small_kernel<T>, dim3((uint32_t)L.nchunks + extra),
+                           dim3(kSupportBlock), 0, s, sa, sync, y_agg, yw, g.cells, zero_cnt, mark);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    } else {
+        hipLaunchKernelGGL(tile_count_kernel, dim3((uint32_t)L.ntiles), dim3(kBlock), 0, s, b,
+                           g.words, last_mask, bvec, L.nchunks, cpre, tcnt);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, tcnt, L.ntiles, ctrl, L.cap);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(support_kernel,
+                           dim3((uint32_t)((L.nchunks + kBlock / 64 - 1) / (kBlock / 64))),
+                           dim3(kBlock), 0, s, sa);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
 
-    // A wave per row when rows are to spare (two or more per SIMD); then, for
-    // int32, round 0 as two passes over the rows (pure_rows, round0_rows)
-    // instead of the counter kernel and the entry-by-entry round, and the peel
-    // kernel starts from round 1 (LSTM, 6.2 M cells: decode 1.40 -> 1.32 ms).
-    const bool wave_rows = planned && (uint64_t)g.rows >= 8ull * (uint64_t)di.cus;
+    // With rows to spare, for int32, round 0 is two passes over the rows
+    // (pure_rows, round0_rows) instead of the counter kernel and the
+    // entry-by-entry round, and the peel kernel starts from round 1 (LSTM,
+    // 6.2 M cells: decode 1.40 -> 1.32 ms).
     // Round 0 by rows works through every member of every live batch twice;
     // it pays when the sketch has at least a cell per support element (the
     // decode's support bound), where it replaces the entry-by-entry round 0.
@@ -2211,6 +2361,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ca.cells = g.cells;
         ca.last_mask = last_mask;
         ca.cstride = kCellStride<A>;
+        ca.split = split;
         // Rows to spare (two or more per SIMD): one wave per row, its loads in
         // flight together.  Fewer, longer rows (NCF: 1.9 K rows of 1.7 K plan
         // entries) keep more waves busy as a workgroup per row, or, when a
@@ -2224,7 +2375,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
             if ((e = launch_rows(counter_rows_kernel<1024>, counter_rows_kernel<512>,
                                  counter_rows_kernel<256>, ca)) != hipSuccess)
                 return e;
-        } else if (3ull * ((g.n + g.c - 1) / g.c) <= kWaveRowsEntries * g.rows) {
+        } else if (few_entries) {
             const uint64_t want = ((uint64_t)g.rows + 3) / 4;  // four waves per workgroup
             const uint32_t cgrid = want < (uint64_t)di.cus * 8 ? (uint32_t)want : (uint32_t)di.cus * 8;
             if (g.c == 1024)
@@ -2234,7 +2385,8 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
             else
                 hipLaunchKernelGGL(counter_wave_kernel<256>, dim3(cgrid), dim3(kBlock), 0, s, ca);
         } else {
-            const uint32_t cgrid = g.rows < (uint32_t)di.cus * 8 ? g.rows : (uint32_t)di.cus * 8;
+            const uint32_t parts = g.rows * split;
+            const uint32_t cgrid = parts < (uint32_t)di.cus * 8 ? parts : (uint32_t)di.cus * 8;
             if (g.c == 1024)
                 hipLaunchKernelGGL(counter_kernel<1024>, dim3(cgrid), dim3(kBlock), 0, s, ca);
             else if (g.c == 512)
@@ -2270,7 +2422,11 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     const uint64_t half_below = fewer_atomics ? kPeelHalfGridCellsInt : kPeelHalfGridCells;
     uint32_t peel_grid = g.cells < half_below && di.cus >= 2 ? (uint32_t)di.cus / 2u
                                                              : (uint32_t)di.cus;
-    if (fewer_atomics && g.cells >= kPeelHalfGridCells && g.cells < half_below && di.cus >= 4)
+    // The fp32 peel, with its paired atomics, from 2 M cells up to its bound too
+    // (LSTM, 6.2 M cells, on half, three quarters and all of the CUs: 1533,
+    // 1456, 1484 us; 2.0 M cells: 789, 780, 816; 1 M and fewer: half).
+    if (di.cus >= 4 && g.cells < half_below &&
+        g.cells >= (fewer_atomics ? kPeelHalfGridCells : g.f32 ? kPeelMostGridCellsF32 : half_below))
         peel_grid = (uint32_t)di.cus / 4u * 3u;
     PeelArgs<A> pa;
     pa.ctrl = ctrl;
@@ -2363,10 +2519,13 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ea.fill = fill_groups != 0 ? &sync->fill.v[0] : nullptr;
         ea.mask_chunks = pa.mask_chunks;
         ea.b_vec = bvec;
+        ea.log2parts = 0;
+        while (ea.log2parts < 4 && (L.nchunks << ea.log2parts) < 4ull * (uint64_t)di.cus) ea.log2parts++;
+        const dim3 egrid((uint32_t)L.nchunks << ea.log2parts);
         if (fill_groups != 0)
-            hipLaunchKernelGGL((emit_kernel<T, true>), dim3((uint32_t)L.nchunks), dim3(kBlock), 0, s, ea);
+            hipLaunchKernelGGL((emit_kernel<T, true>), egrid, dim3(kBlock), 0, s, ea);
         else
-            hipLaunchKernelGGL((emit_kernel<T, false>), dim3((uint32_t)L.nchunks), dim3(kBlock), 0, s, ea);
+            hipLaunchKernelGGL((emit_kernel<T, false>), egrid, dim3(kBlock), 0, s, ea);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

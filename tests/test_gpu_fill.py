@@ -62,8 +62,9 @@ def test_filled_decode_matches(n, kind, vtype):
         for outs in ("x mask coo", "x", "x mask", "x coo", "mask"):
             o, inf = _decode(hc, p, y, b, m, outs.split(), plan)
             assert (inf.success, inf.n_support) == (1, m)
-            if "x_out" in o:
-                assert torch.equal(o["x_out"], x), outs  # whole numbers: exact in fp32 too
+            if "x_out" in o:  # whole numbers: exact in fp32 too
+                bad = torch.nonzero(o["x_out"] != x).reshape(-1)
+                assert bad.numel() == 0, (outs, bad.numel(), bad[:8], o["x_out"][bad[:8]], x[bad[:8]])
             if "mask" in o:
                 assert torch.equal(o["mask"], b), outs
             if "coo_idx" in o:

@@ -90,3 +90,19 @@ def test_small_unaligned_gradient_and_partial_coo(vtype):
     # one worker: fp32 cells of few terms, peeled in fp64
     assert np.array_equal(got, want) if vtype == "i32" else \
         np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want))
+
+
+# past the small paths, few long rows: several workgroups share a row's plan
+# entries (c = 256, 512, 1024), and the bitmap's chunks are shared by the emit
+@pytest.mark.parametrize("n,rows,c,density", [
+    (1_300_007, 4, 1024, 0.0005), (1_300_007, 33, 1024, 0.006), (2_000_003, 7, 512, 0.0004),
+    (1_100_001, 18, 256, 0.001), (4_194_304 + 1, 40, 1024, 0.003),
+])
+def test_few_long_rows_planned(n, rows, c, density):
+    check_int(_w(n, W=2, density=density), rows, c, use_plan=True)
+    check_int(_w(n, W=2, density=density), rows, c, use_plan=False)
+
+
+@pytest.mark.parametrize("n,rows", [(1_300_007, 9), (4_194_304 + 1, 40)])
+def test_few_long_rows_planned_fp32(n, rows):
+    check_fp32(_w(n, "f32", W=2, density=0.2 * rows * 1024 / n), rows, 1024, use_plan=True)
