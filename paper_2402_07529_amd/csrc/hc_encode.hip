@@ -185,6 +185,59 @@ __device__ __forceinline__ void stage_tile(const T (&e)[4][4], const bool (&nz)[
     flush_batch(stage, base, (tbase + 768u) >> log2c, lane, so);
 }
 
+// Bloom-filter inserts of one tile's nonzero words (lanes 0..31, word l the
+// parameters tbase + 32 l ..), for batches of c >= 256: the k hashes of a
+// batch are computed once, one per lane, and a batch with few nonzero words
+// gives each to k lanes at once; with more, the lanes OR their own words hash
+// by hash, which all land in one filter row.  Hashing in every lane for every
+// word bound the encode of sparse gradients (BERT-base at 0.1 %, 13 hashes:
+// 121 us per encode against 62 for the stream).
+constexpr uint32_t kBloomFewWords = 4;
+__device__ __forceinline__ void bloom_insert_tile(uint32_t* __restrict__ f, uint32_t word,
+                                                  uint64_t tbase, uint32_t lane, uint64_t seed,
+                                                  uint32_t k, uint32_t brows, uint32_t c,
+                                                  uint32_t cmask, uint32_t log2c) {
+    const uint32_t cw = c >> 5;  // words per batch, 8 to 32
+    uint32_t left = (uint32_t)__ballot(word != 0u);  // lanes 32.. hold no words
+    while (left != 0u) {
+        const uint32_t q = ((uint32_t)__ffs((int)left) - 1u) / cw;  // batch of the tile
+        const uint32_t in = cw == 32u ? left : left & (((1u << cw) - 1u) << (q * cw));
+        left &= ~in;
+        const BloomHash h =
+            bloom_hash(seed, k, brows, cmask, (tbase >> log2c) + q, lane < k ? lane : 0u);
+        if (__popc(in) <= (int)kBloomFewWords) {
+            const uint32_t hq = h.bias >> 5, r = h.bias & 31u;
+            uint32_t* const rp = f + (uint64_t)h.row * cw;
+            for (uint32_t m = in; m != 0u; m &= m - 1u) {
+                const uint32_t src = (uint32_t)__ffs((int)m) - 1u;
+                const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)word, (int)src);
+                const uint32_t w0 = ((src & (cw - 1u)) + hq) & (cw - 1u);
+                if (lane < k) {
+                    const uint32_t lo = w << r;
+                    if (lo != 0u) atomicOr(rp + w0, lo);
+                    const uint32_t hi = r != 0u ? w >> (32u - r) : 0u;
+                    if (hi != 0u) atomicOr(rp + ((w0 + 1u) & (cw - 1u)), hi);
+                }
+            }
+        } else {
+            const bool mine = lane < 32u && ((in >> lane) & 1u) != 0u;
+            for (uint32_t i = 0; i < k; i++) {
+                const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)h.row, (int)i);
+                const uint32_t bias = (uint32_t)__builtin_amdgcn_readlane((int)h.bias, (int)i);
+                const uint32_t r = bias & 31u;
+                uint32_t* const rp = f + (uint64_t)row * cw;
+                const uint32_t w0 = ((lane & (cw - 1u)) + (bias >> 5)) & (cw - 1u);
+                if (mine) {
+                    const uint32_t lo = word << r;
+                    if (lo != 0u) atomicOr(rp + w0, lo);
+                    const uint32_t hi = r != 0u ? word >> (32u - r) : 0u;
+                    if (hi != 0u) atomicOr(rp + ((w0 + 1u) & (cw - 1u)), hi);
+                }
+            }
+        }
+    }
+}
+
 // One wave tile: 1024 consecutive parameters from `tbase` (a multiple of
 // 1024), four loads of 256 per wave, e[l][k] = parameter tbase + 256 l +
 // 4 lane + k.  Its 32 bitmap words are built from the 16 ballots in lanes
@@ -216,9 +269,9 @@ __device__ __forceinline__ void encode_tile(const T (&e)[4][4], uint64_t tbase, 
     if (!STAGED && any == 0) return;
     // word w = 8 l + i holds parameters 32 w .. 32 w + 31: lanes 8i..8i+7 of
     // load l, parameter 4 lane' + k at bit 4 (lane' - 8 i) + k
+    uint32_t word = 0;
     if (lane < 32) {
         const uint32_t l = lane >> 3, sh = 8u * (lane & 7u);
-        uint32_t word = 0;
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             const uint64_t mk = l == 0 ? m[0][k] : l == 1 ? m[1][k] : l == 2 ? m[2][k] : m[3][k];
@@ -228,10 +281,12 @@ __device__ __forceinline__ void encode_tile(const T (&e)[4][4], uint64_t tbase, 
         if (!BL) {
             // staged: all 32 words of every tile, one full 128-byte line
             if ((STAGED || word != 0u) && widx < words) b[widx] = word;
-        } else if (word != 0u) {
+        } else if (MODE != 0 && word != 0u) {
             bloom_insert_word(b, word, widx << 5, seed, bk, brows, c, cmask, log2c);
         }
     }
+    if (BL && MODE == 0)
+        bloom_insert_tile(b, word, tbase, lane, seed, bk, brows, c, cmask, log2c);
     if (STAGED) {
         stage_tile<T>(e, nz, m, tbase, lane, so, log2c, stage);
         return;
