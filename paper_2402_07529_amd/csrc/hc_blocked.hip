@@ -48,11 +48,6 @@ constexpr uint32_t kSumMask = kDegOne - 1u;
 constexpr uint32_t kClaimed = 0x80000000u;
 constexpr uint32_t kScratchWords = 64;
 constexpr int kAhead = 8;  // global loads a lane keeps in flight in the decode's streaming loops
-// members of 64 words from which lanes walk their own words (measured with
-// the table entries read once per word: 128 against 512 took the decode of
-// BERT-base from 0.253 to 0.240 ms, LSTM 0.157 to 0.154 and VGG19 0.259 to
-// 0.256; BERT-base at 5 % is dense either way)
-constexpr uint32_t kDenseGroup = 128;
 
 // Control block of the blocked decode (zeroed before the decode kernel).
 struct BCtrl {
@@ -135,6 +130,13 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* s_tmp) {
     for (uint32_t w = 0; w < nwaves; w++) t += s_tmp[w];
     lds_barrier();
     return t;
+}
+
+// Keeps the compiler from moving LDS accesses of a wave across this point (the
+// wave's LDS operations complete in order), whatever their types.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ uint32_t load_bword(const uint32_t* b, uint64_t k, uint64_t words,
@@ -731,19 +733,21 @@ __global__ __launch_bounds__(kDecThreads) void decode_blocked_kernel(DecArgs<T> 
                 bool found = true;
                 if (valid) {
                     const uint32_t t = (uint32_t)p & cmask;
-                    A est[3];
-                    found = false;
+                    // the claimed cell's value; only a member without one
+                    // reads all three
+                    uint32_t cell[3];
 #pragma unroll
-                    for (int j = 0; j < 3; j++) {
-                        const uint32_t e = ee[j];
-                        const uint32_t cell = tab_cell(e, t, cmask);
-                        est[j] = Val<A>::sign(s_val[cell], tab_neg(e));
-                        if (s_cnt[cell] == (kClaimed | bl)) {
-                            val = est[j];
-                            found = true;
-                        }
-                    }
-                    if (!found) val = median3(est[0], est[1], est[2]);
+                    for (int j = 0; j < 3; j++) cell[j] = tab_cell(ee[j], t, cmask);
+                    const uint32_t claimed = kClaimed | bl;
+                    const bool f0 = s_cnt[cell[0]] == claimed, f1 = s_cnt[cell[1]] == claimed,
+                               f2 = s_cnt[cell[2]] == claimed;
+                    found = f0 | f1 | f2;
+                    const uint32_t at = f0 ? cell[0] : (f1 ? cell[1] : cell[2]);
+                    const uint32_t e = f0 ? ee[0] : (f1 ? ee[1] : ee[2]);
+                    val = Val<A>::sign(s_val[at], tab_neg(e));
+                    if (!found)
+                        val = median3(Val<A>::sign(s_val[cell[0]], tab_neg(ee[0])),
+                                      Val<A>::sign(s_val[cell[1]], tab_neg(ee[1])), val);
                     const T out = (T)val;
                     if (s < slots) s_stage[s] = out;
                     else if (a.x_out != nullptr) a.x_out[p] = out;
@@ -761,17 +765,35 @@ __global__ __launch_bounds__(kDecThreads) void decode_blocked_kernel(DecArgs<T> 
                     if (!found) atomicAnd(a.mask + (p >> 5), ~(1u << (p & 31u)));
                 }
             };
-            auto member = [&](uint32_t s, bool valid, uint32_t owner, uint32_t bit) {
-                const uint64_t p = (base + owner) * 32ull + bit;
-                const uint32_t bl = valid ? (uint32_t)((p >> a.log2c) - r.b0) : 0u;
-                const uint32_t ee[3] = {s_tab[3 * bl], s_tab[3 * bl + 1], s_tab[3 * bl + 2]};
-                member_e(s, valid, p, bl, ee);
-            };
-            if (total >= kDenseGroup) {
-                // a dense group: each lane walks its own word's members (no
-                // search across lanes for every member; measured on a 73 %
-                // dense BERT-base aggregate).  For c >= 32 the word lies in
-                // one batch, whose table entries are read once.
+            if (total <= slots) {
+                // every lane lists its members' positions in the group at
+                // their ranks, then the lanes take the list 64 at a time and
+                // leave each value in its entry's place.  The listing is a few
+                // instructions a member; walking the words for the values kept
+                // every lane to the fullest word's pace, and finding each
+                // member's owner by search cost more than its value (VGG19
+                // decode, int32 and fp32: 241 and 290 us with those).
+                uint32_t* const list = reinterpret_cast<uint32_t*>(s_stage);
+                uint32_t bits = word, at = excl;
+                wave_lds_order();  // the previous group's values have been read
+                while (bits != 0u) {
+                    list[at++] = 32u * lane + (uint32_t)__builtin_ctz(bits);
+                    bits &= bits - 1u;
+                }
+                wave_lds_order();
+                for (uint32_t s0 = 0; s0 < total; s0 += 64u) {
+                    const uint32_t s = s0 + lane;
+                    const bool valid = s < total;
+                    const uint64_t p = base * 32ull + list[valid ? s : s0];
+                    const uint32_t bl = (uint32_t)((p >> a.log2c) - r.b0);
+                    const uint32_t ee[3] = {s_tab[3 * bl], s_tab[3 * bl + 1], s_tab[3 * bl + 2]};
+                    member_e(s, valid, p, bl, ee);
+                }
+                wave_lds_order();
+            } else {
+                // more members than slots: each lane walks its own word's.
+                // For c >= 32 the word lies in one batch, whose table entries
+                // are read once.
                 uint32_t bits = word, rk = 0;
                 if (a.c >= 32u) {
                     const uint64_t pw = (base + lane) * 32ull;
@@ -787,14 +809,39 @@ __global__ __launch_bounds__(kDecThreads) void decode_blocked_kernel(DecArgs<T> 
                 while (bits != 0u) {
                     const uint32_t bit = (uint32_t)__builtin_ctz(bits);
                     bits &= bits - 1u;
-                    member(excl + rk, true, lane, bit);
+                    const uint64_t p = (base + lane) * 32ull + bit;
+                    const uint32_t bl = (uint32_t)((p >> a.log2c) - r.b0);
+                    const uint32_t ee[3] = {s_tab[3 * bl], s_tab[3 * bl + 1], s_tab[3 * bl + 2]};
+                    member_e(excl + rk, true, p, bl, ee);
                     rk++;
                 }
-            } else {
-                for_each_set_bit(word, member);
             }
             rank += total;
-            if (a.x_out != nullptr) {
+            if (a.x_out != nullptr && total <= slots && a.x_vec && base * 32ull + 2048u <= r.p1) {
+                // a whole group, every value in its slot: a lane's quads hold
+                // the same bits of their words; a quad's values are
+                // consecutive slots, loaded together (the last three may be
+                // past the wave's slots, still within the block's LDS, and are
+                // then not used)
+                const uint32_t sh = 4u * (lane & 7u), below = (1u << sh) - 1u;
+                T* const dst = a.x_out + base * 32ull + 4u * lane;
+#pragma unroll
+                for (uint32_t k = 0; k < 8; k++) {
+                    const uint32_t gw = (uint32_t)__shfl(word, (int)(8u * k + (lane >> 3)));
+                    const uint32_t ge = (uint32_t)__shfl(excl, (int)(8u * k + (lane >> 3)));
+                    const T* const sp = s_stage + ge + __popc(gw & below);
+                    const T s0 = sp[0], s1 = sp[1], s2 = sp[2], s3 = sp[3];
+                    const uint32_t bits = gw >> sh;
+                    const bool b0 = (bits & 1u) != 0u, b1 = (bits & 2u) != 0u,
+                               b2 = (bits & 4u) != 0u, b3 = (bits & 8u) != 0u;
+                    // the next member's value after each bit taken in turn
+                    const T t1 = b0 ? s1 : s0, t2 = b0 ? s2 : s1, t3 = b0 ? s3 : s2;
+                    const T u2 = b1 ? t2 : t1, u3 = b1 ? t3 : t2;
+                    const T w3 = b2 ? u3 : u2;
+                    const V4 z = {b0 ? s0 : T(0), b1 ? t1 : T(0), b2 ? u2 : T(0), b3 ? w3 : T(0)};
+                    __builtin_nontemporal_store(z, reinterpret_cast<V4*>(dst + 256u * k));
+                }
+            } else if (a.x_out != nullptr) {
 #pragma unroll
                 for (int k = 0; k < 8; k++) {
                     const uint32_t off = 256u * k + 4u * lane;  // parameter offset in the group
