@@ -99,9 +99,11 @@ __host__ __device__ __forceinline__ uint32_t block_offsets(uint64_t u, uint32_t 
 // per block independent rotations make that likely).  P_q mixes (it is not
 // affine in i) so that the offsets carry no arithmetic structure, which would
 // itself create small stopping sets.
-__host__ __device__ __forceinline__ BatchHash blocked_local_hash(uint64_t seed, uint32_t brows,
+// (q and i given by the caller; the next function divides for them.)
+__host__ __device__ __forceinline__ BatchHash blocked_batch_hash(uint64_t seed, uint32_t brows,
                                                                  uint32_t cmask, uint32_t log2c,
-                                                                 uint64_t b, uint32_t block) {
+                                                                 uint64_t b, uint64_t q,
+                                                                 uint32_t i) {
     BatchHash h = batch_hash(seed, brows, cmask, b);
     const uint32_t r0 = h.row[0], r1 = h.row[1], r2 = h.row[2];
     const uint32_t lo = r0 < r1 ? (r0 < r2 ? r0 : r2) : (r1 < r2 ? r1 : r2);
@@ -109,12 +111,17 @@ __host__ __device__ __forceinline__ BatchHash blocked_local_hash(uint64_t seed, 
     h.row[0] = lo;
     h.row[1] = r0 + r1 + r2 - lo - hi;
     h.row[2] = hi;
-    const uint64_t q = b / block;
-    const uint32_t i = (uint32_t)(b - q * block);
     const uint32_t pi = block_offsets(splitmix(seed, kBlockSaltBase + q), i, log2c);
     h.bias[1] = (h.bias[0] + (pi & cmask)) & cmask;
     h.bias[2] = (h.bias[0] + (pi >> log2c)) & cmask;
     return h;
+}
+
+__host__ __device__ __forceinline__ BatchHash blocked_local_hash(uint64_t seed, uint32_t brows,
+                                                                 uint32_t cmask, uint32_t log2c,
+                                                                 uint64_t b, uint32_t block) {
+    const uint64_t q = b / block;
+    return blocked_batch_hash(seed, brows, cmask, log2c, b, q, (uint32_t)(b - q * block));
 }
 
 // Hash of batch b with global rows: the global sketch's (block == 0), or a
