@@ -885,6 +885,62 @@ __device__ __forceinline__ void add_live_batches(const CounterArgs& a, bool live
     }
 }
 
+// A batch with at least a quarter of its parameters in the support is taken
+// parameter by parameter instead of word by word: lane l of step i takes
+// parameter 64 i + l, so that consecutive lanes hold consecutive cells (no LDS
+// bank conflicts; a lane per word puts a wave's cells 32 apart) and
+// consecutive ranks (coalesced flags and values, no staging).  Gives f(i,
+// member, rank, column) of each step of batch gb; i is a compile-time constant.
+__device__ __forceinline__ bool dense_batch(uint32_t members, uint32_t c) { return members >= c / 4u; }
+
+template <int C>
+struct DenseBatch {
+    static constexpr uint32_t WPB = C / 32;
+    uint32_t word, pre;  // lane l: word l mod WPB of the batch, members before it
+    __device__ __forceinline__ void load(const CounterArgs& a, uint32_t gb) {
+        const uint32_t wl = lane_id() % WPB;
+        word = load_word_nb(a.b, (uint64_t)gb * WPB + wl, a.words, a.last_mask);
+        const uint32_t pc = __popc(word);
+        uint32_t x = pc;
+#pragma unroll
+        for (uint32_t d = 1; d < WPB; d <<= 1) {
+            const uint32_t y = __shfl_up(x, d);
+            if (wl >= d) x += y;
+        }
+        pre = x - pc;
+    }
+    // parameter 64 i + lane: whether it is a member, and its rank in the batch
+    __device__ __forceinline__ bool member(uint32_t i, uint32_t& rank) const {
+        const uint32_t lane = lane_id(), bit = lane & 31u;
+        const int src = (int)(2u * i + (lane >> 5));
+        const uint32_t w = (uint32_t)__shfl((int)word, src);
+        rank = (uint32_t)__shfl((int)pre, src) + __popc(w & ((1u << bit) - 1u));
+        return ((w >> bit) & 1u) != 0u;
+    }
+};
+
+// add_live_batches for dense batches.
+template <int C>
+__device__ __forceinline__ void add_dense_batches(const CounterArgs& a, bool dense, uint32_t bidx,
+                                                  uint32_t bias, uint32_t boff,
+                                                  unsigned long long* acc) {
+    const uint32_t lane = lane_id();
+    for (uint64_t m = __ballot(dense); m != 0ull; m &= m - 1ull) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        const uint32_t gb = (uint32_t)__builtin_amdgcn_readlane((int)bidx, src);
+        const uint32_t gbias = (uint32_t)__builtin_amdgcn_readlane((int)bias, src);
+        const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)boff, src);
+        DenseBatch<C> d;
+        d.load(a, gb);
+#pragma unroll
+        for (uint32_t i = 0; i < C / 64; i++) {
+            uint32_t rank;
+            if (d.member(i, rank))
+                atomicAdd(&acc[(64u * i + lane + gbias) & (uint32_t)(C - 1)], kOne + off + rank);
+        }
+    }
+}
+
 constexpr uint32_t kScreen = 4;  // chunks of 64 plan entries a row wave screens together
 
 // Screens kScreen chunks of 64 plan entries of a row, from entry cs (< e1):
@@ -893,9 +949,11 @@ constexpr uint32_t kScreen = 4;  // chunks of 64 plan entries a row wave screens
 // rank offset and whether it is live.  Every load is issued unconditionally,
 // at a clamped index, so that the entries' loads are in flight together and
 // then the rank offsets'.
+template <bool D>
 __device__ __forceinline__ void screen_entries(const CounterArgs& a, uint32_t cs, uint32_t e1,
                                                uint32_t (&bidx)[kScreen], uint32_t (&ey)[kScreen],
-                                               uint32_t (&boff)[kScreen], bool (&live)[kScreen]) {
+                                               uint32_t (&boff)[kScreen], bool (&live)[kScreen],
+                                               bool (&dense)[kScreen]) {
     const uint32_t lane = lane_id();
     uint2 ent[kScreen];
 #pragma unroll
@@ -916,7 +974,8 @@ __device__ __forceinline__ void screen_entries(const CounterArgs& a, uint32_t cs
     for (uint32_t h = 0; h < kScreen; h++) {
         ey[h] = ent[h].y;
         boff[h] = lo[h];
-        live[h] = bidx[h] != 0xffffffffu && hi[h] != lo[h];
+        dense[h] = D && bidx[h] != 0xffffffffu && dense_batch(hi[h] - lo[h], a.c);
+        live[h] = bidx[h] != 0xffffffffu && hi[h] != lo[h] && !dense[h];
     }
 }
 
@@ -924,7 +983,7 @@ __device__ __forceinline__ void screen_entries(const CounterArgs& a, uint32_t cs
 // kScreen chunks of 64 plan entries with their loads in flight (a lane per
 // entry: is any member of the support in the batch?), then adds the live
 // batches' members bit by bit (add_live_batches).
-template <int C>
+template <int C, bool D>
 __device__ void build_row(const CounterArgs& a, uint32_t row, unsigned long long* acc) {
     const uint32_t lane = lane_id();
     // a wave's LDS operations complete in order: the previous row's reads are
@@ -933,11 +992,13 @@ __device__ void build_row(const CounterArgs& a, uint32_t row, unsigned long long
     const uint32_t e0 = a.rowoff[row], e1 = a.rowoff[row + 1];
     for (uint32_t cs = e0; cs < e1; cs += 64u * kScreen) {
         uint32_t bidx[kScreen], ey[kScreen], boff[kScreen];
-        bool live[kScreen];
-        screen_entries(a, cs, e1, bidx, ey, boff, live);
+        bool live[kScreen], dense[kScreen];
+        screen_entries<D>(a, cs, e1, bidx, ey, boff, live, dense);
 #pragma unroll
-        for (uint32_t h = 0; h < kScreen; h++)
+        for (uint32_t h = 0; h < kScreen; h++) {
             add_live_batches<C>(a, live[h], bidx[h], ey[h] & 0xffffu, boff[h], acc);
+            if (D) add_dense_batches<C>(a, dense[h], bidx[h], ey[h] & 0xffffu, boff[h], acc);
+        }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // every lane's LDS adds have landed
     __builtin_amdgcn_wave_barrier();
@@ -972,7 +1033,7 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     unsigned long long* const acc = s_acc + wave * C;
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
-        build_row<C>(a, row, acc);
+        build_row<C, false>(a, row, acc);
         unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
         bool fits = true;
         for (uint32_t k = lane; k < (uint32_t)C; k += 64) {
@@ -1013,9 +1074,14 @@ struct Round0Args {
     uint2* queue;
     unsigned int* tail;
     uint32_t log2c;
+    uint32_t round;  // rows_round_kernel: the round it takes (1 or more)
 };
 
-template <int C>
+// Flag byte of an element recovered by rows in round r: bit 0 set, so that the
+// later rounds' claims find it taken, and the round above it.
+__device__ __forceinline__ uint32_t rows_flag(uint32_t r) { return 2u * r + 1u; }
+
+template <int C, bool D>
 __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
     constexpr uint32_t kWaves = kBlock / 64;
     constexpr uint32_t CPL = C / 64;  // cells per lane
@@ -1030,7 +1096,7 @@ __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
     unsigned long long* const acc = s_acc + wave * C;
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
-        build_row<C>(a, row, acc);
+        build_row<C, D>(a, row, acc);
         bool fits = true;
         bool pure[CPL];
         uint32_t pos[CPL], p[CPL];
@@ -1062,7 +1128,9 @@ __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
 // residual in the high word, deg * 2^kp + sum of positions in the low), the
 // flagged members' -g x added to the residual and the others counted;
 // PHASE 1: unpacked counters (deg * 2^32 + sum of positions) of the members
-// not flagged; PHASE 2: the flagged members' -g x in the low word.  The flags
+// not flagged; PHASE 2: the flagged members' -g x in the low word; PHASE 3: as
+// PHASE 0 with only the members flagged in rounds before r.round taken as
+// flagged (other workgroups are setting that round's flags meanwhile).  The flags
 // and values of each batch's first kWin members (ranks are consecutive within
 // a batch) are loaded with the bitmap words, by the batch's WPB lanes, and
 // staged in the wave's window in LDS (win: kR0Unroll * 64 / WPB batches of
@@ -1156,26 +1224,76 @@ __device__ __forceinline__ void sub_live_batches(const Round0Args& r, bool live,
                 const uint32_t bit = (uint32_t)__builtin_ctz(w);
                 w &= w - 1u;
                 const uint32_t fi = rank - fbase, vi = rank - goff[u];
-                const bool fl = (fi < kWin ? wflag[wbase + fi] : r.peeled[rank]) != 0u;
+                const uint32_t fb = fi < kWin ? wflag[wbase + fi] : r.peeled[rank];
+                const bool fl = fb != 0u && (PHASE != 3 || fb < rows_flag(r.round));
                 const uint32_t cell = (32u * wl + bit + bias) & (uint32_t)(C - 1);
                 if (PHASE == 1) {
                     if (!fl) atomicAdd(&acc[cell], kOne + rank);
                 } else if (fl) {
                     const uint32_t xv = vi < kWin ? win[wbase + vi] : (uint32_t)r.vals[rank];
                     const uint32_t gx = neg ? xv : 0u - xv;  // -g x
-                    atomicAdd(&acc[cell], PHASE == 0 ? (unsigned long long)gx << 32
-                                                     : (unsigned long long)gx);
-                } else if (PHASE == 0) {
+                    atomicAdd(&acc[cell], PHASE == 2 ? (unsigned long long)gx
+                                                     : (unsigned long long)gx << 32);
+                } else if (PHASE != 2) {
                     atomicAdd(&acc[cell], (1ull << kp) + rank);
                 }
-                if (PHASE != 2 && fl && j == 0u) e0++;
+                if (PHASE < 2 && fl && j == 0u) e0++;
                 rank++;
             }
         }
     }
 }
 
+// sub_live_batches for dense batches: flags and values come straight from
+// memory, eight steps' loads in flight together.
 template <int C, int PHASE>
+__device__ __forceinline__ void sub_dense_batches(const Round0Args& r, bool dense, uint32_t bidx,
+                                                  uint32_t ey, uint32_t boff,
+                                                  unsigned long long* acc, uint32_t kp,
+                                                  uint32_t nsup, uint32_t& e0) {
+    constexpr uint32_t kSteps = C / 64;
+    constexpr uint32_t kAhead = kSteps < 8 ? kSteps : 8;
+    const uint32_t lane = lane_id();
+    for (uint64_t m = __ballot(dense); m != 0ull; m &= m - 1ull) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        const uint32_t gb = (uint32_t)__builtin_amdgcn_readlane((int)bidx, src);
+        const uint32_t gy = (uint32_t)__builtin_amdgcn_readlane((int)ey, src);
+        const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)boff, src);
+        const uint32_t bias = gy & 0xffffu, j = (gy >> 16) & 3u;
+        const bool neg = (gy >> 31) != 0u;
+        DenseBatch<C> d;
+        d.load(r.c, gb);
+#pragma unroll
+        for (uint32_t i0 = 0; i0 < kSteps; i0 += kAhead) {
+            bool in[kAhead];
+            uint32_t rank[kAhead], fb[kAhead], xv[kAhead];
+#pragma unroll
+            for (uint32_t u = 0; u < kAhead; u++) {
+                in[u] = d.member(i0 + u, rank[u]);
+                rank[u] += off;
+                const uint32_t at = rank[u] < nsup ? rank[u] : 0u;
+                fb[u] = r.peeled[at];
+                xv[u] = PHASE != 1 ? (uint32_t)r.vals[at] : 0u;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kAhead; u++) {
+                const bool fl = fb[u] != 0u && (PHASE != 3 || fb[u] < rows_flag(r.round));
+                unsigned long long inc;
+                if (PHASE == 1) {
+                    inc = fl ? 0ull : kOne + rank[u];
+                } else {
+                    const unsigned long long gx = neg ? xv[u] : 0u - xv[u];  // -g x
+                    if (PHASE == 2) inc = fl ? gx : 0ull;
+                    else inc = fl ? gx << 32 : (1ull << kp) + rank[u];
+                }
+                if (in[u]) atomicAdd(&acc[(64u * (i0 + u) + lane + bias) & (uint32_t)(C - 1)], inc);
+                if (PHASE < 2 && in[u] && fl && j == 0u) e0++;
+            }
+        }
+    }
+}
+
+template <int C, int PHASE, bool D>
 __device__ void round0_row(const Round0Args& r, uint32_t row, unsigned long long* acc,
                            uint32_t* win, uint32_t kp, uint32_t nsup, uint32_t& e0) {
     const CounterArgs& a = r.c;
@@ -1189,16 +1307,19 @@ __device__ void round0_row(const Round0Args& r, uint32_t row, unsigned long long
         y[i] = PHASE == 1 ? 0u : (uint32_t)r.y_agg[(uint64_t)row * C + lane + 64u * i];
 #pragma unroll
     for (uint32_t i = 0; i < CPL; i++)
-        acc[lane + 64u * i] = PHASE == 0 ? (unsigned long long)y[i] << 32 : (unsigned long long)y[i];
+        acc[lane + 64u * i] = PHASE == 0 || PHASE == 3 ? (unsigned long long)y[i] << 32
+                                                       : (unsigned long long)y[i];
     const uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
     for (uint32_t cs = r0; cs < r1; cs += 64u * kScreen) {
         uint32_t bidx[kScreen], ey[kScreen], boff[kScreen];
-        bool live[kScreen];
-        screen_entries(a, cs, r1, bidx, ey, boff, live);
+        bool live[kScreen], dense[kScreen];
+        screen_entries<D>(a, cs, r1, bidx, ey, boff, live, dense);
 #pragma unroll
-        for (uint32_t h = 0; h < kScreen; h++)
+        for (uint32_t h = 0; h < kScreen; h++) {
             sub_live_batches<C, PHASE>(r, live[h], bidx[h], ey[h], boff[h], acc, win, kp, nsup,
                                        e0);
+            if (D) sub_dense_batches<C, PHASE>(r, dense[h], bidx[h], ey[h], boff[h], acc, kp, nsup, e0);
+        }
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // every lane's LDS adds have landed
     __builtin_amdgcn_wave_barrier();
@@ -1241,7 +1362,59 @@ __device__ void round0_write_row(const Round0Args& r, uint32_t row,
     }
 }
 
+// One more round by rows, between pure_rows and round0_rows: each row's packed
+// counters and residuals are built without the elements recovered in earlier
+// rounds, and its pure cells' elements are recovered in place, flagged with
+// this round.  Entry by entry the round costs three scattered atomics per
+// recovered element; here its cost does not depend on how many there are.
+// Counters that do not pack leave the round to the peel kernel, and a round
+// after one that recovered nothing is left out.
 template <int C>
+__global__ __launch_bounds__(kBlock) void rows_round_kernel(Round0Args r) {
+    constexpr uint32_t kWaves = kBlock / 64;
+    constexpr uint32_t CPL = C / 64;
+    constexpr uint32_t kWinWords = kR0Unroll * 64 * 4 + kR0Unroll * 64;
+    __shared__ unsigned long long s_acc[kWaves * C];
+    __shared__ uint32_t s_win[kWaves * kWinWords];
+    const CounterArgs& a = r.c;
+    Ctrl* ctrl = a.ctrl;
+    if ((ctrl->overflow | ctrl->bad_plan | ctrl->nopack) != 0) return;
+    if (r.round > 1u && ctrl->rounds < r.round) return;
+    const uint32_t nsup = (uint32_t)ctrl->n_support;
+    const uint32_t kp = pack_bits(nsup);
+    const uint32_t lane = lane_id();
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    unsigned long long* const acc = s_acc + wave * C;
+    uint32_t* const win = s_win + wave * kWinWords;
+    const uint32_t nwaves = gridDim.x * kWaves;
+    uint32_t e0 = 0;
+    bool any = false;
+    for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
+        round0_row<C, 3, true>(r, row, acc, win, kp, nsup, e0);
+        bool pure[CPL];
+        uint32_t pos[CPL], p[CPL], y[CPL];
+#pragma unroll
+        for (uint32_t i = 0; i < CPL; i++) {
+            const unsigned long long v = acc[lane + 64u * i];
+            pos[i] = (uint32_t)v & ((1u << kp) - 1u);
+            pure[i] = ((uint32_t)v >> kp) == 1u && pos[i] < nsup;
+            y[i] = (uint32_t)(v >> 32);
+            p[i] = r.elem[pure[i] ? pos[i] : 0u];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < CPL; i++) {
+            if (!pure[i]) continue;
+            any = true;
+            const BatchHash h = batch_hash(a.seed, a.rows, a.cmask, p[i] >> r.log2c);
+            const uint32_t j = h.row[0] == row ? 0u : (h.row[1] == row ? 1u : 2u);
+            r.vals[pos[i]] = Val<int32_t>::sign((int32_t)y[i], (h.neg >> j) & 1u);
+            r.peeled[pos[i]] = (uint8_t)rows_flag(r.round);
+        }
+    }
+    if (__ballot(any) != 0ull && lane == 0) atomicMax(&ctrl->rounds, r.round + 1u);
+}
+
+template <int C, bool D>
 __global__ __launch_bounds__(kBlock) void round0_rows_kernel(Round0Args r) {
     constexpr uint32_t kWaves = kBlock / 64;
     // per wave: the row's counters, and the window of kR0Unroll * 64 * 4
@@ -1266,12 +1439,12 @@ __global__ __launch_bounds__(kBlock) void round0_rows_kernel(Round0Args r) {
     uint32_t e0 = 0;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
         if (packed) {
-            round0_row<C, 0>(r, row, acc, win, kp, nsup, e0);
+            round0_row<C, 0, D>(r, row, acc, win, kp, nsup, e0);
             round0_write_row<C>(r, row, acc, true, kp);
         } else {
-            round0_row<C, 1>(r, row, acc, win, kp, nsup, e0);
+            round0_row<C, 1, D>(r, row, acc, win, kp, nsup, e0);
             round0_write_row<C>(r, row, acc, false, kp);
-            round0_row<C, 2>(r, row, acc, win, kp, nsup, e0);
+            round0_row<C, 2, D>(r, row, acc, win, kp, nsup, e0);
             for (uint32_t k = lane; k < (uint32_t)C; k += 64)
                 r.yw[(uint64_t)row * C + k] = (int32_t)(uint32_t)acc[k];
         }
@@ -1304,6 +1477,7 @@ struct PeelArgs {  // T: the decode-side arithmetic type
     uint32_t rows, c, cmask, log2c, cells;
     bool counted;   // a counter kernel built the counters (and checked their packing)
     bool split0;    // round 0 ran before the peel kernel, as whole-chip launches
+    uint32_t rows_rounds;  // further rounds run by rows if the counters pack
     // the workgroups from peel_groups on zero the dense outputs while the
     // others peel: mask_chunks chunks of fill_mask, then fill_x's, fill_chunks in all
     uint32_t peel_groups;
@@ -1717,7 +1891,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 
         uint32_t qs = a.split0 ? sync->round0.v[0] : 0u;
         if (qs > a.cells) qs = a.cells;
-        for (uint32_t r = a.split0 ? 1u : 0u; ok; r++) {
+        for (uint32_t r = a.split0 ? 1u + (packed ? a.rows_rounds : 0u) : 0u; ok; r++) {
             uint32_t qe = fend;
             if (qe > a.cells) qe = a.cells;  // the queue holds each cell at most once
             if (qe <= qs) break;
@@ -2342,7 +2516,16 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     // to 0.6 of n the decode took 2.35-3.68 ms by rows against 1.18-3.37 ms
     // without, and from 0.7 up 4.78-7.57 ms against 4.85-14.5 ms.
     const bool rows0 = wave_rows && std::is_same<T, int32_t>::value && (uint64_t)g.cells >= L.cap;
+    // Supports of a quarter of the parameters or more (by the bound): most
+    // batches are dense ones, and three further rounds go by rows.  VGG19 at
+    // 69.6 % and a cell per parameter: round trip 15.56 ms, 15.00 with dense
+    // batches taken by parameter, 13.63 and 11.91 with one and three more
+    // rounds by rows.  At 5.9 % the dense batches' code alone cost the decode
+    // 1.5 % (1.675 against 1.700 ms), and each further round 50 us or more.
+    const bool dense_rows = rows0 && L.cap >= g.n / 4;
+    const uint32_t rows_rounds = dense_rows ? 3u : 0u;
     Round0Args ra;
+    ra.round = 0;
     ra.y_agg = reinterpret_cast<const int32_t*>(y_agg_v);
     ra.vals = reinterpret_cast<int32_t*>(vals);
     ra.peeled = peeled;
@@ -2399,9 +2582,17 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         // row has only a few entries, a wave per row walking them in turn.
         if (rows0) {
             ra.c = ca;
-            if ((e = launch_rows(pure_rows_kernel<1024>, pure_rows_kernel<512>,
-                                 pure_rows_kernel<256>, ra)) != hipSuccess)
-                return e;
+            e = dense_rows ? launch_rows(pure_rows_kernel<1024, true>, pure_rows_kernel<512, true>,
+                                         pure_rows_kernel<256, true>, ra)
+                           : launch_rows(pure_rows_kernel<1024, false>, pure_rows_kernel<512, false>,
+                                         pure_rows_kernel<256, false>, ra);
+            if (e != hipSuccess) return e;
+            for (uint32_t k = 1; k <= rows_rounds; k++) {
+                ra.round = k;
+                if ((e = launch_rows(rows_round_kernel<1024>, rows_round_kernel<512>,
+                                     rows_round_kernel<256>, ra)) != hipSuccess)
+                    return e;
+            }
         } else if (wave_rows) {
             if ((e = launch_rows(counter_rows_kernel<1024>, counter_rows_kernel<512>,
                                  counter_rows_kernel<256>, ca)) != hipSuccess)
@@ -2478,12 +2669,15 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     pa.log2c = g.log2c;
     pa.cells = g.cells;
     pa.counted = planned;
+    pa.rows_rounds = rows_rounds;
     // large sketches (large round-0 frontiers) take round 0 on the whole chip
     pa.split0 = rows0 || g.cells >= kRound0SplitCells;  // round 0 ran before the peel kernel
     if (rows0) {
-        if ((e = launch_rows(round0_rows_kernel<1024>, round0_rows_kernel<512>,
-                             round0_rows_kernel<256>, ra)) != hipSuccess)
-            return e;
+        e = dense_rows ? launch_rows(round0_rows_kernel<1024, true>, round0_rows_kernel<512, true>,
+                                     round0_rows_kernel<256, true>, ra)
+                       : launch_rows(round0_rows_kernel<1024, false>, round0_rows_kernel<512, false>,
+                                     round0_rows_kernel<256, false>, ra);
+        if (e != hipSuccess) return e;
     } else if (pa.split0) {
         const uint32_t grid0 = (uint32_t)di.cus * 8;
         hipLaunchKernelGGL(scan0_kernel<A>, dim3(grid0), dim3(kBlock), 0, s, pa);
