@@ -654,8 +654,9 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
     __shared__ uint32_t s_boff[kStage];
     __shared__ uint2 s_live[kBlock];
     __shared__ uint32_t s_tmp[kWaves];
-    // loaded together with the first row's bounds: tested one after the other,
-    // each of the three costs a memory latency before the row begins
+    // header and control block are loaded together; the row's bounds only once
+    // the header has matched (a plan of another geometry may be shorter than
+    // this row's place in it)
     const PlanHeader hdr = *a.hdr;
     const uint32_t overflow = a.ctrl->overflow;
     const unsigned long long nsup = a.ctrl->n_support;
@@ -663,8 +664,6 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
     const uint32_t wave = threadIdx.x >> 6;
     const uint32_t nparts = a.rows * a.split;
     uint32_t part = blockIdx.x;  // < nparts: the grid has at most that many
-    uint32_t row = part / a.split;
-    uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
     if (!(hdr.magic == kPlanMagic && hdr.n == a.n && hdr.seed == a.seed && hdr.c == a.c &&
           hdr.rows == a.rows)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) a.ctrl->bad_plan = 1u;
@@ -672,6 +671,8 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
     }
     if (overflow) return;
     const uint32_t kpack = pack_bits(nsup);
+    uint32_t row = part / a.split;
+    uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
     for (;;) {
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) s_acc[k] = 0ull;
         const uint32_t len = (r1 - r0 + a.split - 1u) / a.split;
