@@ -59,16 +59,23 @@ constexpr uint32_t kPeelPushCap = 8 * kPeelBlock;  // staged frontier entries pe
 constexpr uint64_t kPeelHalfGridCells = 8ull << 20;  // below this many cells the peel uses half the CUs
 constexpr uint64_t kPeelMostGridCellsF32 = 2ull << 20;  // fp32: three quarters from here to that bound
 constexpr uint64_t kPeelHalfGridCellsInt = 32ull << 20;  // the same with residuals in the counters
-constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a packed counter
+constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a counter (count_bits = 32)
 
 // The fp32 decode keeps each cell's counter and fp64 residual side by side in
 // one 16-byte record: counter i is 64-bit word 2 i and its residual word
 // 2 i + 1.  The int32 decode keeps two arrays.
 template <typename T> constexpr uint32_t kCellStride = std::is_same<T, double>::value ? 2u : 1u;
 // With at most 2^kPairBits support elements the fp32 peel holds the counters
-// as doubles, deg * 2^k + (sum of positions) < 2^53, always exact (see
-// peel_pairs).
+// as doubles, deg * 2^kPairBits + (sum of positions) < 2^53, always exact (see
+// peel_pairs).  They are built in that form as 64-bit integers: from counters
+// of deg * 2^32 + sum the two could not be told apart where the sum passes
+// 2^32.
 constexpr uint32_t kPairBits = 26;
+
+// Bits below the degree in the counters as they are built.
+__device__ __forceinline__ uint32_t count_bits(bool f32, uint64_t nsup) {
+    return f32 && nsup <= (1ull << kPairBits) ? kPairBits : 32u;
+}
 
 // The int32 peel can carry a cell's residual in its counter word: value in
 // the high 32 bits, deg * 2^k + (sum of member positions) in the low 32, with
@@ -338,16 +345,17 @@ struct SupportArgs {
 };
 
 // Element pos of E is parameter p: its list entry, its cleared flag and,
-// without a plan, its three counter increments.  Positions past the capacity
-// are dropped (the decode then reports overflow).
-__device__ __forceinline__ void support_put(const SupportArgs& a, uint32_t pos, uint32_t p) {
+// without a plan, its three counter increments (one: an incidence).  Positions
+// past the capacity are dropped (the decode then reports overflow).
+__device__ __forceinline__ void support_put(const SupportArgs& a, uint32_t pos, uint32_t p,
+                                            unsigned long long one) {
     if (pos >= a.cap) return;
     a.elem[pos] = p;
     a.peeled[pos] = 0u;
     if (a.woffb == nullptr) {
         const BatchHash h = batch_hash(a.seed, a.rows, a.cmask, p >> a.log2c);
         const uint32_t t = p & a.cmask;
-        const unsigned long long inc = kOne + pos;
+        const unsigned long long inc = one + pos;
 #pragma unroll
         for (int j = 0; j < 3; j++)
             atomicAdd(a.cnt + (uint64_t)a.cstride * cell_of(h, j, t, a.c, a.cmask), inc);
@@ -359,12 +367,13 @@ constexpr uint32_t kWaveStage = 1024;  // elements one wave stages in LDS at a t
 // The wave stores stage[0, total) as E[base + j], consecutive lanes on
 // consecutive elements.  Every lane has written its stage entries.
 __device__ __forceinline__ void support_flush(const SupportArgs& a, uint32_t* stage,
-                                              uint32_t total, uint32_t base, uint32_t lane) {
+                                              uint32_t total, uint32_t base, uint32_t lane,
+                                              unsigned long long one) {
     if (total == 0) return;
     // the wave's LDS writes are complete before any lane reads them back
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
-    for (uint32_t j = lane; j < total; j += 64) support_put(a, base + j, stage[j]);
+    for (uint32_t j = lane; j < total; j += 64) support_put(a, base + j, stage[j], one);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();  // the stage is refilled next
 }
@@ -390,6 +399,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
     uint32_t base = a.toff[chunk / kTileChunks] + a.cpre[chunk];
     if (lane == 0) a.blk[chunk] = base;
     const uint64_t wmask = (1ull << a.log2wpb) - 1ull;
+    const unsigned long long one = 1ull << count_bits(a.cstride == 2u, a.ctrl->n_support);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const uint32_t w4[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -418,7 +428,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
             if (!staged) o += __popc(w4[k]);
         }
         if (staged) {
-            support_flush(a, stage, total, base, lane);
+            support_flush(a, stage, total, base, lane, one);
         } else {
             // over 1/8 dense: eight passes of 32 words, two lanes per word
             // (16 bits each), at most 1024 elements a pass
@@ -440,7 +450,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
                     stage[q++] = (uint32_t)(w * 32u) + 16u * half + (uint32_t)__builtin_ctz(bits);
                     bits &= bits - 1u;
                 }
-                support_flush(a, stage, ptotal, pbase, lane);
+                support_flush(a, stage, ptotal, pbase, lane, one);
                 pbase += ptotal;
             }
         }
@@ -497,8 +507,10 @@ __global__ __launch_bounds__(kSupportBlock) void support_small_kernel(
         a.woffb[w >> a.log2wpb] = base + excl;
     const uint32_t wave = uniform(tid >> 6);
     const uint32_t wbase = base + uniform(excl);  // lane 0's rank: the wave's first
+    static_assert(kSmallChunks * kChunkBits <= (1ull << kPairBits), "count_bits without |S|");
+    const unsigned long long one = 1ull << count_bits(a.cstride == 2u, 0);
     for_each_set_bit(word, [&](uint32_t s, bool valid, uint32_t owner, uint32_t bit) {
-        if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit);
+        if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit, one);
     });
     if (blockIdx.x == nchunks - 1u) {
         if (tid < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(a.ctrl)[tid] = 0u;
@@ -625,8 +637,8 @@ struct CounterArgs {
 // One workgroup per sketch row (grid-stride), or `split` workgroups per row,
 // each taking a run of its plan entries.  Cell k of row r gathers, from
 // every (batch b, hash j) in the row's plan entry list, the parameter
-// t = (k - bias_j(b)) mod c of batch b: if its bit is set it adds 2^32 + its
-// rank in the support.  Integer sums, so the result equals the atomic build
+// t = (k - bias_j(b)) mod c of batch b: if its bit is set it adds an incidence
+// (2^count_bits) + its rank in the support.  Integer sums, so the result equals the atomic build
 // exactly whatever the order.  Every step issues its global loads together,
 // so a row costs a few memory latencies however many batches land on it:
 //   screen  each lane takes one plan entry (kBlock at a time) and checks
@@ -670,6 +682,8 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         return;
     }
     if (overflow) return;
+    const bool f32 = a.cstride == 2u;
+    const unsigned long long one = 1ull << count_bits(f32, nsup);
     const uint32_t kpack = pack_bits(nsup);
     uint32_t row = part / a.split;
     uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
@@ -718,7 +732,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
                         if ((word >> bit) & 1u) {
                             const uint32_t rank = (first ? off_a : off_b) +
                                                   __popc(word & ((1u << bit) - 1u));
-                            atomicAdd(&s_acc[lane * CPL + i], kOne + rank);
+                            atomicAdd(&s_acc[lane * CPL + i], one + rank);
                         }
                     }
                 }
@@ -734,7 +748,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
             unsigned long long* const dst = a.cnt + (uint64_t)a.cstride * (row * C + k);
             if (a.split == 1u) *dst = acc;
             else if (acc != 0ull) atomicAdd(dst, acc);
-            fits = fits && fits_packed_share(acc, kpack, a.split);
+            fits = fits && (f32 || fits_packed_share(acc, kpack, a.split));
         }
         flag_unpackable(a.ctrl, fits);
         part += gridDim.x;
@@ -766,7 +780,10 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
         return;
     }
     if (a.ctrl->overflow) return;
-    const uint32_t kpack = pack_bits(a.ctrl->n_support);
+    const unsigned long long nsup = a.ctrl->n_support;
+    const bool f32 = a.cstride == 2u;
+    const unsigned long long one = 1ull << count_bits(f32, nsup);
+    const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
     unsigned long long* const acc = s_acc + wave * C;
@@ -806,7 +823,7 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
                     if ((word >> bit) & 1u) {
                         const uint32_t rank = (first ? off_a : off_b) +
                                               __popc(word & ((1u << bit) - 1u));
-                        acc[lane * CPL + i] += kOne + rank;
+                        acc[lane * CPL + i] += one + rank;
                     }
                 }
             }
@@ -817,7 +834,7 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
         for (uint32_t i = 0; i < CPL; i++) {
             const unsigned long long v = acc[i * 64u + lane];
             dst[a.cstride * (i * 64u + lane)] = v;
-            fits = fits && fits_packed(v, kpack);
+            fits = fits && (f32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
     }
@@ -831,7 +848,7 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
 template <int C>
 __device__ __forceinline__ void add_live_batches(const CounterArgs& a, bool live, uint32_t bidx,
                                                  uint32_t bias, uint32_t boff,
-                                                 unsigned long long* acc) {
+                                                 unsigned long long* acc, unsigned long long one) {
     constexpr uint32_t WPB = C / 32;       // bitmap words per batch
     constexpr uint32_t kGroup = 64 / WPB;  // batches per wave-wide load
     constexpr uint32_t kUnroll = 4;        // wave-wide loads in flight
@@ -879,7 +896,7 @@ __device__ __forceinline__ void add_live_batches(const CounterArgs& a, bool live
             while (w != 0u) {
                 const uint32_t bit = (uint32_t)__builtin_ctz(w);
                 w &= w - 1u;
-                atomicAdd(&acc[(32u * wl + bit + gbias[u]) & (uint32_t)(C - 1)], kOne + rank);
+                atomicAdd(&acc[(32u * wl + bit + gbias[u]) & (uint32_t)(C - 1)], one + rank);
                 rank++;
             }
         }
@@ -985,7 +1002,8 @@ __device__ __forceinline__ void screen_entries(const CounterArgs& a, uint32_t cs
 // entry: is any member of the support in the batch?), then adds the live
 // batches' members bit by bit (add_live_batches).
 template <int C, bool D>
-__device__ void build_row(const CounterArgs& a, uint32_t row, unsigned long long* acc) {
+__device__ void build_row(const CounterArgs& a, uint32_t row, unsigned long long* acc,
+                          unsigned long long one) {
     const uint32_t lane = lane_id();
     // a wave's LDS operations complete in order: the previous row's reads are
     // done before these stores
@@ -997,7 +1015,7 @@ __device__ void build_row(const CounterArgs& a, uint32_t row, unsigned long long
         screen_entries<D>(a, cs, e1, bidx, ey, boff, live, dense);
 #pragma unroll
         for (uint32_t h = 0; h < kScreen; h++) {
-            add_live_batches<C>(a, live[h], bidx[h], ey[h] & 0xffffu, boff[h], acc);
+            add_live_batches<C>(a, live[h], bidx[h], ey[h] & 0xffffu, boff[h], acc, one);
             if (D) add_dense_batches<C>(a, dense[h], bidx[h], ey[h] & 0xffffu, boff[h], acc);
         }
     }
@@ -1028,19 +1046,22 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     __shared__ unsigned long long s_acc[kWaves * C];
     if (!plan_matches(a)) return;
     if (a.ctrl->overflow) return;
-    const uint32_t kpack = pack_bits(a.ctrl->n_support);
+    const unsigned long long nsup = a.ctrl->n_support;
+    const bool f32 = a.cstride == 2u;
+    const unsigned long long one = 1ull << count_bits(f32, nsup);
+    const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
     unsigned long long* const acc = s_acc + wave * C;
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
-        build_row<C, false>(a, row, acc);
+        build_row<C, false>(a, row, acc, one);
         unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
         bool fits = true;
         for (uint32_t k = lane; k < (uint32_t)C; k += 64) {
             const unsigned long long v = acc[k];
             dst[a.cstride * k] = v;
-            fits = fits && fits_packed(v, kpack);
+            fits = fits && (f32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
     }
@@ -1097,7 +1118,7 @@ __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
     unsigned long long* const acc = s_acc + wave * C;
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
-        build_row<C, D>(a, row, acc);
+        build_row<C, D>(a, row, acc, kOne);
         bool fits = true;
         bool pure[CPL];
         uint32_t pos[CPL], p[CPL];
@@ -1503,19 +1524,27 @@ __device__ __forceinline__ void scan_residual(const PeelArgs<T>& a, uint64_t cid
         else
             __hip_atomic_store(a.yw + cidx, (int32_t)y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-        // fp32: the residual is in the record already; the counter becomes a double
+        // fp32: the residual is in the record already; the counter, built with
+        // kPairBits (kp) below the degree, becomes a double
         if (!packed || cidx >= a.cells) return;
-        const double d = (double)(((v >> 32) << kp) + (v & 0xffffffffull));
-        st_agent64(a.cnt + 2 * cidx, __builtin_bit_cast(unsigned long long, d));
+        st_agent64(a.cnt + 2 * cidx, __builtin_bit_cast(unsigned long long, (double)v));
     }
 }
 
+// Bits below the degree in the fused form's counters.
+template <typename T> __device__ __forceinline__ uint32_t peel_bits(uint64_t nsup) {
+    return std::is_same<T, int32_t>::value ? pack_bits(nsup) : kPairBits;
+}
 // Whether the peel runs its fused form: int32 with the residuals in the
 // counter words, or fp32 with the counters as doubles.
 template <typename T>
-__device__ __forceinline__ bool peel_packed(const PeelArgs<T>& a, uint32_t kp) {
+__device__ __forceinline__ bool peel_packed(const PeelArgs<T>& a, uint64_t nsup) {
     if constexpr (std::is_same<T, int32_t>::value) return a.counted && a.ctrl->nopack == 0;
-    return kp <= kPairBits;
+    return count_bits(true, nsup) == kPairBits;
+}
+// Bits below the degree in the counters that the round-0 scan reads.
+template <typename T> __device__ __forceinline__ uint32_t scan_bits(bool packed) {
+    return !std::is_same<T, int32_t>::value && packed ? kPairBits : 32u;
 }
 
 // One frontier entry (cell cidx, element position pos): whether it recovers
@@ -1858,9 +1887,10 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 
     if (!skip) {
         const uint32_t nsup = (uint32_t)ctrl->n_support;
-        const uint32_t kp = pack_bits(nsup);
-        const bool packed = peel_packed(a, kp);
+        const uint32_t kp = peel_bits<T>(nsup);
+        const bool packed = peel_packed(a, nsup);
         if (!a.split0) {
+            const uint32_t sb = scan_bits<T>(packed);
             // round 0's frontier is every cell with exactly one element;
             // packed, each counter also takes its cell's residual in its high
             // word.  Four cells per lane and pass, loaded together, then staged.
@@ -1878,7 +1908,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
                 for (uint32_t m = 0; m < kScanCells; m++) {
                     const uint64_t cidx = base + m * nthreads + gtid;
                     scan_residual(a, cidx, v[m], packed, kp);
-                    lds_push(q, (v[m] >> 32) == 1ull, (uint32_t)cidx, (uint32_t)v[m]);
+                    lds_push(q, (v[m] >> sb) == 1ull, (uint32_t)cidx, (uint32_t)(v[m] - (1ull << sb)));
                 }
                 flush_pushes(q, false, kScanCells * kPeelBlock, &sync->tail.v[0], a.queue,
                              a.cells, a.mark, 1u);
@@ -1984,8 +2014,10 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
     if (ctrl->overflow != 0 || ctrl->bad_plan != 0) return;
     if (threadIdx.x == 0) q.count = 0;
     lds_barrier();
-    const uint32_t kp = pack_bits((uint32_t)ctrl->n_support);
-    const bool packed = peel_packed(a, kp);
+    const uint32_t nsup = (uint32_t)ctrl->n_support;
+    const uint32_t kp = peel_bits<T>(nsup);
+    const bool packed = peel_packed(a, nsup);
+    const uint32_t sb = scan_bits<T>(packed);
     const uint64_t nthreads = (uint64_t)gridDim.x * kBlock;
     const uint64_t gtid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     for (uint64_t base = 0; base < a.cells; base += kScanCells * nthreads) {
@@ -1999,7 +2031,7 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
         for (uint32_t m = 0; m < kScanCells; m++) {
             const uint64_t cidx = base + m * nthreads + gtid;
             scan_residual(a, cidx, v[m], packed, kp);
-            lds_push(q, (v[m] >> 32) == 1ull, (uint32_t)cidx, (uint32_t)v[m]);
+            lds_push(q, (v[m] >> sb) == 1ull, (uint32_t)cidx, (uint32_t)(v[m] - (1ull << sb)));
         }
         flush_pushes(q, false, kScanCells * kBlock, &a.sync->tail.v[0], a.queue, a.cells,
                      a.mark, 1u);
@@ -2024,8 +2056,8 @@ __global__ __launch_bounds__(kBlock) void round0_kernel(PeelArgs<T> a) {
     }
     lds_barrier();
     const uint32_t nsup = (uint32_t)ctrl->n_support;
-    const uint32_t kp = pack_bits(nsup);
-    const bool packed = peel_packed(a, kp);
+    const uint32_t kp = peel_bits<T>(nsup);
+    const bool packed = peel_packed(a, nsup);
     uint32_t qe = a.sync->round0.v[0];
     if (qe > a.cells) qe = a.cells;
     uint32_t my_recovered = 0, my_last_round = 0;
