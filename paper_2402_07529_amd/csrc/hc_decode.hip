@@ -2441,7 +2441,7 @@ __global__ __launch_bounds__(kBlock) void bloom_probe_kernel(
 template <typename T>
 hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
                            const uint32_t* b, const DecodeOut& out, const DecodeLayout& L,
-                           void* ws, hipStream_t s) {
+                           void* ws, bool in_place, hipStream_t s) {
     char* base = static_cast<char*>(ws);
     typedef typename Acc<T>::type A;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(base + L.ctrl);
@@ -2730,7 +2730,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     // writes at the full rate (48 of 256 workgroups 1124 us on the 2^30 case,
     // 64 945, 96 939, 128 959; the smaller cases are best at 24 to 64).
     uint32_t fill_groups = 0;
-    if (out.x_out != nullptr && x_vec && mask_vec && L.cap <= g.n / 64) {
+    if (!in_place && out.x_out != nullptr && x_vec && mask_vec && L.cap <= g.n / 64) {
         fill_groups = (uint32_t)di.cus - peel_grid;
         if (fill_groups > (uint32_t)di.cus / 4u) fill_groups = (uint32_t)di.cus / 4u;
     }
@@ -2778,7 +2778,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ea.mask_chunks = pa.mask_chunks;
         ea.b_vec = bvec;
         ea.log2parts = 0;
-        while (ea.log2parts < 4 && (L.nchunks << ea.log2parts) < 4ull * (uint64_t)di.cus) ea.log2parts++;
+        while (!in_place && ea.log2parts < 4 && (L.nchunks << ea.log2parts) < 4ull * (uint64_t)di.cus) ea.log2parts++;
         const dim3 egrid((uint32_t)L.nchunks << ea.log2parts);
         if (fill_groups != 0)
             hipLaunchKernelGGL((emit_kernel<T, true>), egrid, dim3(kBlock), 0, s, ea);
@@ -2790,6 +2790,18 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Whether any output of the decode shares memory with [in, in + bytes).
+bool outputs_overlap(const Geo& g, const DecodeOut& out, const void* in, size_t bytes) {
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(in), hi = lo + bytes;
+    auto meets = [&](const void* p, uint64_t words) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+        return p != nullptr && a < hi && a + words * 4 > lo;
+    };
+    const uint64_t entries = out.coo_cap < g.n ? out.coo_cap : g.n;
+    return meets(out.x_out, g.n) || meets(out.mask, g.words) || meets(out.coo_idx, entries) ||
+           meets(out.coo_val, entries);
+}
 
 }  // namespace
 
@@ -2859,9 +2871,16 @@ hipError_t launch_decode(const Geo& g, const void* plan, const void* y_agg, cons
         if (e != hipSuccess) return e;
         b_agg = cand;
     }
-    if (whole_decode_fits(g)) return launch_decode_whole(g, plan, y_agg, b_agg, out, L.cap, s);
-    if (g.f32) return launch_decode_t<float>(g, plan, y_agg, b_agg, out, L, ws, s);
-    return launch_decode_t<int32_t>(g, plan, y_agg, b_agg, out, L, ws, s);
+    // A caller done with the aggregate may decode over it (the mask into the
+    // bitmap, the sum into the sketch's buffer).  That holds where a workgroup
+    // writes only words that no other reads later: not in the whole-sketch
+    // decode, beside the peel, or where workgroups share an emit chunk.
+    const bool in_place = outputs_overlap(g, out, y_agg, (size_t)g.cells * 4) ||
+                          (g.bloom_k == 0 && outputs_overlap(g, out, b_agg, (size_t)g.words * 4));
+    if (!in_place && whole_decode_fits(g))
+        return launch_decode_whole(g, plan, y_agg, b_agg, out, L.cap, s);
+    if (g.f32) return launch_decode_t<float>(g, plan, y_agg, b_agg, out, L, ws, in_place, s);
+    return launch_decode_t<int32_t>(g, plan, y_agg, b_agg, out, L, ws, in_place, s);
 }
 
 }  // namespace hc
