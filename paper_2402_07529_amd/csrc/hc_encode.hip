@@ -186,55 +186,42 @@ __device__ __forceinline__ void stage_tile(const T (&e)[4][4], const bool (&nz)[
 }
 
 // Bloom-filter inserts of one tile's nonzero words (lanes 0..31, word l the
-// parameters tbase + 32 l ..), for batches of c >= 256: the k hashes of a
-// batch are computed once, one per lane, and a batch with few nonzero words
-// gives each to k lanes at once; with more, the lanes OR their own words hash
-// by hash, which all land in one filter row.  Hashing in every lane for every
-// word bound the encode of sparse gradients (BERT-base at 0.1 %, 13 hashes:
-// 121 us per encode against 62 for the stream).
-constexpr uint32_t kBloomFewWords = 4;
+// parameters tbase + 32 l ..), for batches of c >= 256: W' = 2^lw lanes per
+// hash, W' the number of nonzero words rounded up, and 64 / W' hashes at a
+// time, so that ceil(k W' / 64) steps insert all.  A lane for every word with
+// the k hashes in turn left almost all lanes idle on sparse gradients
+// (BERT-base at 0.1 %, 13 hashes: 121 us per encode against 62 for the
+// stream).  The words of one hash sit in neighbouring lanes: a batch's words
+// land in one filter row, and an atomic costs per 64-byte line it touches in
+// a wave instruction, not per lane (hashes in neighbouring lanes, word by
+// word: 103 us at 0.3 % of 50 M parameters with c = 1024, 86 so; at 0.1 % 48.5
+// and 45.5).
 __device__ __forceinline__ void bloom_insert_tile(uint32_t* __restrict__ f, uint32_t word,
                                                   uint64_t tbase, uint32_t lane, uint64_t seed,
                                                   uint32_t k, uint32_t brows, uint32_t c,
                                                   uint32_t cmask, uint32_t log2c) {
     const uint32_t cw = c >> 5;  // words per batch, 8 to 32
-    uint32_t left = (uint32_t)__ballot(word != 0u);  // lanes 32.. hold no words
-    while (left != 0u) {
-        const uint32_t q = ((uint32_t)__ffs((int)left) - 1u) / cw;  // batch of the tile
-        const uint32_t in = cw == 32u ? left : left & (((1u << cw) - 1u) << (q * cw));
-        left &= ~in;
-        const BloomHash h =
-            bloom_hash(seed, k, brows, cmask, (tbase >> log2c) + q, lane < k ? lane : 0u);
-        if (__popc(in) <= (int)kBloomFewWords) {
-            const uint32_t hq = h.bias >> 5, r = h.bias & 31u;
-            uint32_t* const rp = f + (uint64_t)h.row * cw;
-            for (uint32_t m = in; m != 0u; m &= m - 1u) {
-                const uint32_t src = (uint32_t)__ffs((int)m) - 1u;
-                const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)word, (int)src);
-                const uint32_t w0 = ((src & (cw - 1u)) + hq) & (cw - 1u);
-                if (lane < k) {
-                    const uint32_t lo = w << r;
-                    if (lo != 0u) atomicOr(rp + w0, lo);
-                    const uint32_t hi = r != 0u ? w >> (32u - r) : 0u;
-                    if (hi != 0u) atomicOr(rp + ((w0 + 1u) & (cw - 1u)), hi);
-                }
-            }
-        } else {
-            const bool mine = lane < 32u && ((in >> lane) & 1u) != 0u;
-            for (uint32_t i = 0; i < k; i++) {
-                const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)h.row, (int)i);
-                const uint32_t bias = (uint32_t)__builtin_amdgcn_readlane((int)h.bias, (int)i);
-                const uint32_t r = bias & 31u;
-                uint32_t* const rp = f + (uint64_t)row * cw;
-                const uint32_t w0 = ((lane & (cw - 1u)) + (bias >> 5)) & (cw - 1u);
-                if (mine) {
-                    const uint32_t lo = word << r;
-                    if (lo != 0u) atomicOr(rp + w0, lo);
-                    const uint32_t hi = r != 0u ? word >> (32u - r) : 0u;
-                    if (hi != 0u) atomicOr(rp + ((w0 + 1u) & (cw - 1u)), hi);
-                }
-            }
-        }
+    const uint32_t live = (uint32_t)__ballot(word != 0u);  // lanes 32.. hold no words
+    const uint32_t nw = __popc(live);
+    if (nw == 0u) return;
+    const uint32_t lw = nw == 1u ? 0u : 32u - (uint32_t)__builtin_clz(nw - 1u);
+    const uint32_t ws = lane & ((1u << lw) - 1u);  // which nonzero word
+    const uint32_t src = nw == 1u ? (uint32_t)__builtin_ctz(live)
+                         : lw == 5u ? ws
+                                    : select_bit(live, ws < nw ? ws : 0u);
+    uint32_t w = (uint32_t)__shfl((int)word, (int)src);
+    if (lw != 5u && ws >= nw) w = 0u;
+    if (w == 0u) return;
+    const uint64_t batch = (tbase + 32u * src) >> log2c;
+    const uint32_t ow = src & (cw - 1u);
+    for (uint32_t i = lane >> lw; i < k; i += 64u >> lw) {
+        const BloomHash h = bloom_hash(seed, k, brows, cmask, batch, i);
+        const uint32_t r = h.bias & 31u, w0 = (ow + (h.bias >> 5)) & (cw - 1u);
+        uint32_t* const rp = f + (uint64_t)h.row * cw;
+        const uint32_t lo = w << r;
+        if (lo != 0u) atomicOr(rp + w0, lo);
+        const uint32_t hi = r != 0u ? w >> (32u - r) : 0u;
+        if (hi != 0u) atomicOr(rp + ((w0 + 1u) & (cw - 1u)), hi);
     }
 }
 
