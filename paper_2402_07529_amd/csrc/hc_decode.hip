@@ -64,7 +64,8 @@ constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a counter (
 // The fp32 decode keeps each cell's counter and fp64 residual side by side in
 // one 16-byte record: counter i is 64-bit word 2 i and its residual word
 // 2 i + 1.  The int32 decode keeps two arrays.
-template <typename T> constexpr uint32_t kCellStride = std::is_same<T, double>::value ? 2u : 1u;
+template <bool F32> constexpr uint32_t kCounterStride = F32 ? 2u : 1u;
+template <typename T> constexpr uint32_t kCellStride = kCounterStride<std::is_same<T, double>::value>;
 // With at most 2^kPairBits support elements the fp32 peel holds the counters
 // as doubles, deg * 2^kPairBits + (sum of positions) < 2^53, always exact (see
 // peel_pairs).  They are built in that form as 64-bit integers: from counters
@@ -72,9 +73,11 @@ template <typename T> constexpr uint32_t kCellStride = std::is_same<T, double>::
 // 2^32.
 constexpr uint32_t kPairBits = 26;
 
-// Bits below the degree in the counters as they are built.
-__device__ __forceinline__ uint32_t count_bits(bool f32, uint64_t nsup) {
-    return f32 && nsup <= (1ull << kPairBits) ? kPairBits : 32u;
+// Bits below the degree in the counters as they are built.  (Constant for
+// int32: read from a register, the counter kernel's adds cost 1 % of a decode
+// of 60 M parameters.)
+template <bool F32> __device__ __forceinline__ uint32_t count_bits(uint64_t nsup) {
+    return F32 && nsup <= (1ull << kPairBits) ? kPairBits : 32u;
 }
 
 // The int32 peel can carry a cell's residual in its counter word: value in
@@ -399,7 +402,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
     uint32_t base = a.toff[chunk / kTileChunks] + a.cpre[chunk];
     if (lane == 0) a.blk[chunk] = base;
     const uint64_t wmask = (1ull << a.log2wpb) - 1ull;
-    const unsigned long long one = 1ull << count_bits(a.cstride == 2u, a.ctrl->n_support);
+    const unsigned long long one = 1ull << (a.cstride == 2u ? count_bits<true>(a.ctrl->n_support) : 32u);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const uint32_t w4[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -508,7 +511,7 @@ __global__ __launch_bounds__(kSupportBlock) void support_small_kernel(
     const uint32_t wave = uniform(tid >> 6);
     const uint32_t wbase = base + uniform(excl);  // lane 0's rank: the wave's first
     static_assert(kSmallChunks * kChunkBits <= (1ull << kPairBits), "count_bits without |S|");
-    const unsigned long long one = 1ull << count_bits(a.cstride == 2u, 0);
+    const unsigned long long one = 1ull << (a.cstride == 2u ? count_bits<true>(0) : 32u);
     for_each_set_bit(word, [&](uint32_t s, bool valid, uint32_t owner, uint32_t bit) {
         if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit, one);
     });
@@ -630,7 +633,6 @@ struct CounterArgs {
     Ctrl* ctrl;
     uint64_t n, seed, words, nb;
     uint32_t rows, c, cmask, cells, last_mask;
-    uint32_t cstride;  // 64-bit words from one counter to the next
     uint32_t split;    // counter_kernel: workgroups sharing a row's entries
 };
 
@@ -656,7 +658,7 @@ constexpr uint32_t kStage = 64;  // live batches staged in LDS at a time
 constexpr uint64_t kSplitEntries = 32;    // plan entries a part of a split row has at least, on average
 constexpr uint64_t kWaveRowsEntries = 8;  // plan entries per row up to which a wave takes a row
 
-template <int C>
+template <int C, bool F32>
 __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
     constexpr uint32_t WPB = C / 32;  // bitmap words per batch
     constexpr uint32_t CPL = C / 64;  // cells per lane
@@ -682,8 +684,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         return;
     }
     if (overflow) return;
-    const bool f32 = a.cstride == 2u;
-    const unsigned long long one = 1ull << count_bits(f32, nsup);
+    const unsigned long long one = 1ull << count_bits<F32>(nsup);
     const uint32_t kpack = pack_bits(nsup);
     uint32_t row = part / a.split;
     uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
@@ -745,10 +746,10 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         bool fits = true;
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) {
             const unsigned long long acc = s_acc[k];
-            unsigned long long* const dst = a.cnt + (uint64_t)a.cstride * (row * C + k);
+            unsigned long long* const dst = a.cnt + (uint64_t)kCounterStride<F32> * (row * C + k);
             if (a.split == 1u) *dst = acc;
             else if (acc != 0ull) atomicAdd(dst, acc);
-            fits = fits && (f32 || fits_packed_share(acc, kpack, a.split));
+            fits = fits && (F32 || fits_packed_share(acc, kpack, a.split));
         }
         flag_unpackable(a.ctrl, fits);
         part += gridDim.x;
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
 // words and rank offsets, every lane takes the (at most two) words covering
 // its C/64 consecutive cells by shuffle and adds into its own cells of the
 // wave's copy of the row in LDS.  The row is written with plain stores.
-template <int C>
+template <int C, bool F32>
 __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
     constexpr uint32_t WPB = C / 32;  // bitmap words per batch
     constexpr uint32_t CPL = C / 64;  // cells per lane
@@ -781,8 +782,7 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
     }
     if (a.ctrl->overflow) return;
     const unsigned long long nsup = a.ctrl->n_support;
-    const bool f32 = a.cstride == 2u;
-    const unsigned long long one = 1ull << count_bits(f32, nsup);
+    const unsigned long long one = 1ull << count_bits<F32>(nsup);
     const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
@@ -828,13 +828,13 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
                 }
             }
         }
-        unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * kCounterStride<F32>;
         bool fits = true;
 #pragma unroll
         for (uint32_t i = 0; i < CPL; i++) {
             const unsigned long long v = acc[i * 64u + lane];
-            dst[a.cstride * (i * 64u + lane)] = v;
-            fits = fits && (f32 || fits_packed(v, kpack));
+            dst[kCounterStride<F32> * (i * 64u + lane)] = v;
+            fits = fits && (F32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
     }
@@ -1040,15 +1040,14 @@ __device__ __forceinline__ bool plan_matches(const CounterArgs& a) {
 // counters went from 178 to 101 us); with few long rows (NCF: 1.9 K rows of
 // 1.7 K entries, a few dense words per batch) it left SIMDs idle and ran
 // twice as long as counter_kernel.
-template <int C>
+template <int C, bool F32>
 __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     constexpr uint32_t kWaves = kBlock / 64;
     __shared__ unsigned long long s_acc[kWaves * C];
     if (!plan_matches(a)) return;
     if (a.ctrl->overflow) return;
     const unsigned long long nsup = a.ctrl->n_support;
-    const bool f32 = a.cstride == 2u;
-    const unsigned long long one = 1ull << count_bits(f32, nsup);
+    const unsigned long long one = 1ull << count_bits<F32>(nsup);
     const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
@@ -1056,12 +1055,12 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
         build_row<C, false>(a, row, acc, one);
-        unsigned long long* dst = a.cnt + (uint64_t)row * C * a.cstride;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * kCounterStride<F32>;
         bool fits = true;
         for (uint32_t k = lane; k < (uint32_t)C; k += 64) {
             const unsigned long long v = acc[k];
-            dst[a.cstride * k] = v;
-            fits = fits && (f32 || fits_packed(v, kpack));
+            dst[kCounterStride<F32> * k] = v;
+            fits = fits && (F32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
     }
@@ -1540,7 +1539,7 @@ template <typename T> __device__ __forceinline__ uint32_t peel_bits(uint64_t nsu
 template <typename T>
 __device__ __forceinline__ bool peel_packed(const PeelArgs<T>& a, uint64_t nsup) {
     if constexpr (std::is_same<T, int32_t>::value) return a.counted && a.ctrl->nopack == 0;
-    return count_bits(true, nsup) == kPairBits;
+    return count_bits<true>(nsup) == kPairBits;
 }
 // Bits below the degree in the counters that the round-0 scan reads.
 template <typename T> __device__ __forceinline__ uint32_t scan_bits(bool packed) {
@@ -2591,6 +2590,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     };
 
     if (planned) {
+        constexpr bool kF32 = std::is_same<T, float>::value;
         const PlanLayout PL = plan_layout(g);
         const char* pb = static_cast<const char*>(plan);
         CounterArgs ca;
@@ -2610,7 +2610,6 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ca.cmask = g.cmask;
         ca.cells = g.cells;
         ca.last_mask = last_mask;
-        ca.cstride = kCellStride<A>;
         ca.split = split;
         // Rows to spare (two or more per SIMD): one wave per row, its loads in
         // flight together.  Fewer, longer rows (NCF: 1.9 K rows of 1.7 K plan
@@ -2630,27 +2629,27 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
                     return e;
             }
         } else if (wave_rows) {
-            if ((e = launch_rows(counter_rows_kernel<1024>, counter_rows_kernel<512>,
-                                 counter_rows_kernel<256>, ca)) != hipSuccess)
+            if ((e = launch_rows(counter_rows_kernel<1024, kF32>, counter_rows_kernel<512, kF32>,
+                                 counter_rows_kernel<256, kF32>, ca)) != hipSuccess)
                 return e;
         } else if (few_entries) {
             const uint64_t want = ((uint64_t)g.rows + 3) / 4;  // four waves per workgroup
             const uint32_t cgrid = want < (uint64_t)di.cus * 8 ? (uint32_t)want : (uint32_t)di.cus * 8;
             if (g.c == 1024)
-                hipLaunchKernelGGL(counter_wave_kernel<1024>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_wave_kernel<1024, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
             else if (g.c == 512)
-                hipLaunchKernelGGL(counter_wave_kernel<512>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_wave_kernel<512, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
             else
-                hipLaunchKernelGGL(counter_wave_kernel<256>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_wave_kernel<256, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
         } else {
             const uint32_t parts = g.rows * split;
             const uint32_t cgrid = parts < (uint32_t)di.cus * 8 ? parts : (uint32_t)di.cus * 8;
             if (g.c == 1024)
-                hipLaunchKernelGGL(counter_kernel<1024>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_kernel<1024, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
             else if (g.c == 512)
-                hipLaunchKernelGGL(counter_kernel<512>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_kernel<512, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
             else
-                hipLaunchKernelGGL(counter_kernel<256>, dim3(cgrid), dim3(kBlock), 0, s, ca);
+                hipLaunchKernelGGL((counter_kernel<256, kF32>), dim3(cgrid), dim3(kBlock), 0, s, ca);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
