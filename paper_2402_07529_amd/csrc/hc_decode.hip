@@ -2779,8 +2779,15 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ea.fill = fill_groups != 0 ? &sync->fill.v[0] : nullptr;
         ea.mask_chunks = pa.mask_chunks;
         ea.b_vec = bvec;
+        // Chunks are shared until the grid reaches the eight workgroups that fit
+        // on a CU: with fewer they are all in flight at once and the time is one
+        // workgroup's (60 M parameters at 3 %, 1832 chunks: decode 489 us whole,
+        // 472 shared by two; from 75 M on nothing changes).  Four per CU where
+        // only words with members are written (8 M at 0.5 %: 142 us on four,
+        // 143 on eight).
+        const uint64_t want = (fill_groups != 0 ? 4ull : 8ull) * (uint64_t)di.cus;
         ea.log2parts = 0;
-        while (!in_place && ea.log2parts < 4 && (L.nchunks << ea.log2parts) < 4ull * (uint64_t)di.cus) ea.log2parts++;
+        while (!in_place && ea.log2parts < 4 && (L.nchunks << ea.log2parts) < want) ea.log2parts++;
         const dim3 egrid((uint32_t)L.nchunks << ea.log2parts);
         if (fill_groups != 0)
             hipLaunchKernelGGL((emit_kernel<T, true>), egrid, dim3(kBlock), 0, s, ea);
