@@ -1102,6 +1102,31 @@ struct Round0Args {
 // later rounds' claims find it taken, and the round above it.
 __device__ __forceinline__ uint32_t rows_flag(uint32_t r) { return 2u * r + 1u; }
 
+// Rounds after round 0 that go by rows for a support of nsup elements, 0 for
+// sparse supports, whose batches are not taken parameter by parameter either.
+// Dense batches pay from half the parameters on, and one round by rows with
+// them; the more of the support a round recovers the more of them pay, that is
+// with cells to spare.  Decodes of 5 to 80 M parameters against the plain row
+// passes (time / time; support / n, cells / support):
+//              no round  one   two   three rounds
+//   0.25, 1.25    1.01   1.05  1.12  1.21   (20 M)
+//   0.25, 1.5     1.03   1.02  1.04  1.08
+//   0.35, 1.25    0.99   1.00  1.04  1.09
+//   0.35, 1.5     1.00   0.96  0.95  0.96   (8 M: 0.98 one, 1.07 three)
+//   0.5,  1.25    0.99   0.98  1.00  1.04   (80 M: 0.95 one, 0.98 three)
+//   0.5,  1.5     0.99   0.92  0.89  0.88   (80 M: 0.89 one, 0.80 three)
+//   0.75, 1.25    0.97   0.95  0.95  0.97
+//   0.75, 1.5     0.95   0.86  0.80  0.76
+// At c = 256, whose passes cost more per element, one round stays the best
+// (0.7, 1.4: 0.927, three 0.936; 0.5, 1.4: 0.975, three 1.03).
+__host__ __device__ __forceinline__ uint32_t rows_rounds(uint64_t n, uint64_t cells, uint32_t c,
+                                                         uint64_t nsup) {
+    const bool spare = c >= 512u && 5u * cells >= 7u * nsup;
+    if (nsup < (spare ? n / 3u : n / 2u)) return 0u;
+    return spare && nsup >= n / 2u ? 3u : 1u;
+}
+
+// D: the support may be dense, by its bound; whether it is, n_support tells.
 template <int C, bool D>
 __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
     constexpr uint32_t kWaves = kBlock / 64;
@@ -1116,8 +1141,10 @@ __global__ __launch_bounds__(kBlock) void pure_rows_kernel(Round0Args r) {
     const uint32_t wave = uniform(threadIdx.x >> 6);
     unsigned long long* const acc = s_acc + wave * C;
     const uint32_t nwaves = gridDim.x * kWaves;
+    const bool dense = D && rows_rounds(a.n, a.cells, a.c, nsup) != 0u;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
-        build_row<C, D>(a, row, acc, kOne);
+        if (D && dense) build_row<C, true>(a, row, acc, kOne);
+        else build_row<C, false>(a, row, acc, kOne);
         bool fits = true;
         bool pure[CPL];
         uint32_t pos[CPL], p[CPL];
@@ -1388,8 +1415,8 @@ __device__ void round0_write_row(const Round0Args& r, uint32_t row,
 // rounds, and its pure cells' elements are recovered in place, flagged with
 // this round.  Entry by entry the round costs three scattered atomics per
 // recovered element; here its cost does not depend on how many there are.
-// Counters that do not pack leave the round to the peel kernel, and a round
-// after one that recovered nothing is left out.
+// Counters that do not pack leave the round to the peel kernel, sparse supports
+// too (rows_rounds), and a round after one that recovered nothing is left out.
 template <int C>
 __global__ __launch_bounds__(kBlock) void rows_round_kernel(Round0Args r) {
     constexpr uint32_t kWaves = kBlock / 64;
@@ -1402,6 +1429,7 @@ __global__ __launch_bounds__(kBlock) void rows_round_kernel(Round0Args r) {
     if ((ctrl->overflow | ctrl->bad_plan | ctrl->nopack) != 0) return;
     if (r.round > 1u && ctrl->rounds < r.round) return;
     const uint32_t nsup = (uint32_t)ctrl->n_support;
+    if (r.round > rows_rounds(a.n, a.cells, a.c, nsup)) return;
     const uint32_t kp = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
@@ -1458,9 +1486,11 @@ __global__ __launch_bounds__(kBlock) void round0_rows_kernel(Round0Args r) {
     uint32_t* const win = s_win + wave * kWinWords;
     const uint32_t nwaves = gridDim.x * kWaves;
     uint32_t e0 = 0;
+    const bool dense = D && rows_rounds(a.n, a.cells, a.c, nsup) != 0u;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
         if (packed) {
-            round0_row<C, 0, D>(r, row, acc, win, kp, nsup, e0);
+            if (D && dense) round0_row<C, 0, true>(r, row, acc, win, kp, nsup, e0);
+            else round0_row<C, 0, false>(r, row, acc, win, kp, nsup, e0);
             round0_write_row<C>(r, row, acc, true, kp);
         } else {
             round0_row<C, 1, D>(r, row, acc, win, kp, nsup, e0);
@@ -1498,7 +1528,8 @@ struct PeelArgs {  // T: the decode-side arithmetic type
     uint32_t rows, c, cmask, log2c, cells;
     bool counted;   // a counter kernel built the counters (and checked their packing)
     bool split0;    // round 0 ran before the peel kernel, as whole-chip launches
-    uint32_t rows_rounds;  // further rounds run by rows if the counters pack
+    uint32_t row_launches;  // further rounds launched by rows, of which rows_rounds ran if the
+    uint64_t n;             // counters pack
     // the workgroups from peel_groups on zero the dense outputs while the
     // others peel: mask_chunks chunks of fill_mask, then fill_x's, fill_chunks in all
     uint32_t peel_groups;
@@ -1921,7 +1952,9 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 
         uint32_t qs = a.split0 ? sync->round0.v[0] : 0u;
         if (qs > a.cells) qs = a.cells;
-        for (uint32_t r = a.split0 ? 1u + (packed ? a.rows_rounds : 0u) : 0u; ok; r++) {
+        uint32_t r = a.split0 ? 1u : 0u;
+        if (a.row_launches != 0u && packed) r += min(a.row_launches, rows_rounds(a.n, a.cells, a.c, nsup));
+        for (; ok; r++) {
             uint32_t qe = fend;
             if (qe > a.cells) qe = a.cells;  // the queue holds each cell at most once
             if (qe <= qs) break;
@@ -2551,14 +2584,17 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     // to 0.6 of n the decode took 2.35-3.68 ms by rows against 1.18-3.37 ms
     // without, and from 0.7 up 4.78-7.57 ms against 4.85-14.5 ms.
     const bool rows0 = wave_rows && std::is_same<T, int32_t>::value && (uint64_t)g.cells >= L.cap;
-    // Supports of a quarter of the parameters or more (by the bound): most
-    // batches are dense ones, and three further rounds go by rows.  VGG19 at
-    // 69.6 % and a cell per parameter: round trip 15.56 ms, 15.00 with dense
-    // batches taken by parameter, 13.63 and 11.91 with one and three more
-    // rounds by rows.  At 5.9 % the dense batches' code alone cost the decode
-    // 1.5 % (1.675 against 1.700 ms), and each further round 50 us or more.
-    const bool dense_rows = rows0 && L.cap >= g.n / 4;
-    const uint32_t rows_rounds = dense_rows ? 3u : 0u;
+    // Further rounds by rows: a bound below n is taken for the support, without
+    // one as many are launched as any support may take.  Each leaves at once
+    // where the support itself takes fewer, which costs a sparse decode that
+    // names no bound up to 2 or 3 % in a sketch as wide as the gradient (20 M
+    // parameters, 0.1 to 30 % dense); the rounds chosen by the bound alone cost
+    // it 10 to 45 %.
+    uint32_t row_launches = rows0 ? rows_rounds(g.n, g.cells, g.c, L.cap) : 0u;
+    if (rows0 && L.cap == g.n)
+        for (const uint64_t m : {g.n / 3, g.n / 2})
+            row_launches = std::max(row_launches, rows_rounds(g.n, g.cells, g.c, m));
+    const bool dense_rows = row_launches != 0;
     Round0Args ra;
     ra.round = 0;
     ra.y_agg = reinterpret_cast<const int32_t*>(y_agg_v);
@@ -2622,7 +2658,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
                            : launch_rows(pure_rows_kernel<1024, false>, pure_rows_kernel<512, false>,
                                          pure_rows_kernel<256, false>, ra);
             if (e != hipSuccess) return e;
-            for (uint32_t k = 1; k <= rows_rounds; k++) {
+            for (uint32_t k = 1; k <= row_launches; k++) {
                 ra.round = k;
                 if ((e = launch_rows(rows_round_kernel<1024>, rows_round_kernel<512>,
                                      rows_round_kernel<256>, ra)) != hipSuccess)
@@ -2704,7 +2740,8 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     pa.log2c = g.log2c;
     pa.cells = g.cells;
     pa.counted = planned;
-    pa.rows_rounds = rows_rounds;
+    pa.row_launches = row_launches;
+    pa.n = g.n;
     // large sketches (large round-0 frontiers) take round 0 on the whole chip
     pa.split0 = rows0 || g.cells >= kRound0SplitCells;  // round 0 ran before the peel kernel
     if (rows0) {
