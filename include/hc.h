@@ -302,11 +302,14 @@ hc_status hc_aggregate(const hc_params *p, const void *y_in, const uint32_t *b_i
  *   info (one struct)     summary, DEVICE memory.
  * ws/ws_bytes: device workspace of at least the ws_bytes hc_sizes reports for
  * the same max_support; contents on entry are ignored.  max_support also picks
- * how round 0 runs on an int32 sketch with a plan: by rows when the sketch has
- * a cell per element of max_support, entry by entry otherwise (a bound near
- * the true support keeps the faster one; results are the same either way).
+ * how round 0 runs on an int32 sketch with a plan (by rows when the sketch has
+ * a cell per element of max_support, entry by entry otherwise), how many
+ * further rounds may run by rows, and whether the dense outputs are zeroed
+ * beside the peel (a bound near the true support keeps the faster forms;
+ * results are the same either way).
  * Peeling runs as synchronous rounds entirely on the device (one cooperative
- * kernel; no host round trips).  Decode failure is data (info->success), not
+ * kernel, or for a sketch that fits one workgroup's LDS one ordinary launch
+ * for the whole decode; no host round trips).  Decode failure is data (info->success), not
  * an error status. */
 hc_status hc_decode(const hc_params *p, const void *plan, const void *y_agg,
                     const uint32_t *b_agg,

@@ -1121,8 +1121,9 @@ hipError_t launch_decode_whole_t(const Geo& g, const void* plan, const void* y_a
 }  // namespace
 
 // The whole-sketch decode serves every global sketch it can hold: at most 1024
-// batches (packed counters) whose cells, table and queue fit one workgroup's
-// LDS (at c = 1024 up to 14 rows for int32, 10 for fp32).  It beat the general
+// batches (packed counters) whose cells, table, queue and member counts fit one
+// workgroup's LDS: at c = 1024 up to 14 rows for int32 and 10 for fp32, one
+// more up to 640 batches (int32) and 347 (fp32).  It beat the general
 // path's nine launches at every such size measured (1 % and 0.1 % density, us
 // per decode from Python, general against this): n = 65,536 114 against 18,
 // 262,144 174 against 25, 1,000,003 225 against 60 (int32, 17 rounds).

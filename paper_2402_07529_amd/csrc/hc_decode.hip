@@ -1,47 +1,59 @@
 // hc_decode.hip -- recovery (Algorithm 1, phase II) for gfx950.
 //
-// Stages (one stream, no host round trips):
-//   prep     copy the aggregated sketch into a residual Yw (fp64 for fp32
-//            gradients), clear the control block (and, without a plan, the
-//            per-cell counters);
+// A global sketch that fits one workgroup's LDS is decoded by one launch
+// (decode_blocked_kernel in hc_blocked.hip, the sketch as its only block).
+// Otherwise, stages on one stream, no host round trips:
+//   prep     clear the control block, copy the aggregated sketch into a
+//            residual (fp64 beside the counter for fp32 gradients; int32
+//            without a plan), clear counters that are built by atomics;
 //   count    popcount of the bitmap per tile of 16 chunks of 1024 words, and
 //            each chunk's offset within its tile;
 //   scan     exclusive scan of the tile counts (one workgroup) -> offsets and
 //            the support size |S|;
 //   support  one wave per chunk: the set bits become the ascending element
 //            list E (section 3.2: the index names every nonzero parameter)
-//            and, with a plan, every batch's rank offset;
+//            and, with a plan, every batch's rank offset.  Up to 128 chunks
+//            the four steps are one launch (support_small_kernel);
 //   counters per cell  cnt = deg * 2^32 + (sum of member positions):  a cell
 //            is pure (one live element) exactly when cnt >> 32 == 1, and then
-//            its low word is that element's position.  With a plan (the
-//            inverse row map of hc_plan.hip) one workgroup per sketch row
-//            gathers its counters from the bitmap words of the batches that
-//            land on it -- no atomics.  Without a plan every element adds
+//            its low word is that element's position (fp32 with at most 2^26
+//            elements: 2^26 in place of 2^32).  With a plan (the
+//            inverse row map of hc_plan.hip) the counters are
+//            gathered row by row from the bitmap words of the batches that
+//            land on it, without atomics but where workgroups share a row.
+//            Without a plan every element adds
 //            itself to its three cells with 64-bit atomics;
 //   round 0  a scan queues the pure cells (round 0's frontier) and, for large
 //            sketches, round 0 is peeled, both as ordinary launches over the
-//            whole chip; for smaller ones the peel kernel does both itself;
+//            whole chip; for smaller ones the peel kernel does both itself.
+//            int32 sketches with rows to spare take round 0 as passes over the
+//            rows, and dense supports up to three further rounds;
 //   peel     one cooperative persistent kernel running the later synchronous
 //            rounds (section 3.2, parallel peeling).  The frontier of round r is the
 //            list of (cell, element) pairs whose cell became pure during round
-//            r-1, kept in one append-only queue.  An element owning several
+//            r-1, kept in one append-only queue.  An int32 element owning several
 //            frontier cells is claimed by an atomic OR on its flag byte: the
 //            first of its frontier entries to get there recovers
 //            x = g_j * Y from its cell (every pure cell of the element holds the
-//            same value, exactly so in integer arithmetic), and subtracts g * x
-//            and the element from its other two cells with atomics (int32 with
-//            a plan: one per cell, the residual riding in the counter word); a
+//            same value exactly); an fp32 one is recovered through its frontier
+//            cell of smallest j, which the cells' marks tell.  It subtracts g * x
+//            and the element from its other two cells with atomics (one per
+//            cell for int32 with a plan, the residual riding in the counter
+//            word, and one per lane pair for fp32, counter and residual side by
+//            side as doubles); a
 //            cell whose count drops to one joins the next frontier.  Entries whose element
 //            is already taken (in this round or an earlier one) do nothing, so
 //            the elements peeled in round r are exactly those with a cell in
 //            its frontier that were still live when it began.
 //            One grid barrier per round (workgroup-scope fences: what a round
 //            hands to the next goes through atomics and coherent loads and
-//            stores); rounds end when a frontier is empty;
+//            stores); rounds end when a frontier is empty.  For sparse supports
+//            further workgroups zero the dense outputs meanwhile;
 //   leftovers  elements never peeled get the Count Sketch median estimate
 //            from the residual sketch (Algorithm 1, last recovery step), on
 //            the whole chip: when decoding fails most of the support is left;
-//   emit     dense output, recovered mask and COO from E and the values.
+//   emit     dense output, recovered mask and COO from E and the values (only
+//            the words with members where the outputs were zeroed beside the peel).
 #include <algorithm>
 #include <type_traits>
 
@@ -1770,15 +1782,9 @@ __device__ __forceinline__ void peel_step(const PeelArgs<T>& a, bool have, uint2
     lds_push(q, push[1], oc[1], ppos[1]);
 }
 
-// Grid-wide barrier in two levels: the workgroups of group g (blockIdx % G)
-// arrive on the group's counter, the last of each group on the top counter,
-// and the last of those publishes the end of the next frontier and bumps the
-// generation that everyone polls.  Each workgroup makes its writes visible
-// with one release fence before arriving and picks up everyone else's with
-// one acquire fence after the wait; group leaders pass their group's writes on
-// with an acquire-release fence.  The wait polls with relaxed loads, so
-// spinning workgroups do not keep invalidating their caches.  gen is the
-// number of barriers the grid has passed (every workgroup counts them, and the
+// Grid-wide barrier on one counter: every workgroup arrives on it, and the
+// last publishes the end of the next frontier with the generation that everyone
+// polls.  Its fences are workgroup-scope (see inside).  gen is the number of barriers the grid has passed (every workgroup counts them, and the
 // control block starts at zero), so arriving needs no load.  *fend gets the
 // next frontier's end.  Returns false if this workgroup's wait timed out (it
 // sets ctrl->abort for the summary; any other workgroup still waiting then
@@ -2176,8 +2182,6 @@ struct EmitArgs {  // T: the gradient type; values are kept in Acc<T>
     bool x_vec;     // x_out is 16-byte aligned
     bool mask_vec;  // mask is 16-byte aligned
     bool b_vec;     // b is 16-byte aligned
-    const unsigned int* fill;  // chunks zeroed beside the peel (FILLED)
-    uint32_t mask_chunks;      // of them the mask's, which come first
 };
 
 template <typename T>
@@ -2236,8 +2240,8 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
     }
     lds_barrier();
     const uint64_t chunk_p = chunk * kChunkBits;
-    if (FILLED && chunk + a.mask_chunks < a.fill[0] && total <= kEmitStage) {
-        // zeroed beside the peel: write the words that hold members, two words
+    if (FILLED && total <= kEmitStage) {
+        // zeroed beside the peel, whose launch ends with every chunk filled: write the words that hold members, two words
         // at a time per wave, half a wave on each (whole 128-byte lines, so
         // that no line is read back to be completed).  A shared chunk's
         // workgroups each take a run of every wave's lanes; left to one of
@@ -2400,23 +2404,25 @@ __global__ __launch_bounds__(kBlock) void emit_kernel(EmitArgs<T> a) {
 // the two filter words covering them, shifted back by the rotation, give the
 // hash's 32 answers at once; the word is their AND over i (stopping once it is
 // zero).  Below c = 32 each parameter is checked bit by bit.
-// For c >= 1024 a wave's 64 words are two batches: each half computes its
+// For c = 1024 a wave's 64 words are two batches: each half computes its
 // batch's first 32 hashes once, one per lane (every word hashing for itself
-// was most of the probe: 56 us for BERT-base and 13 hashes).
+// was most of the probe: 56 us for BERT-base and 13 hashes).  Narrower batches
+// hash per word.
 __global__ __launch_bounds__(kBlock) void bloom_probe_kernel(
     const uint32_t* __restrict__ f, uint32_t* __restrict__ cand, uint64_t n, uint64_t words,
     uint64_t seed, uint32_t k, uint32_t brows, uint32_t c, uint32_t cmask, uint32_t log2c,
     uint32_t last_mask) {
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t w = (uint64_t)blockIdx.x * kBlock + threadIdx.x; w < words; w += stride) {
-        // all 64 lanes of the wave are in the loop
+        // whether all 64 lanes of the wave are in the loop
         const bool full = (w | 63u) < words;
         const uint64_t p0 = w << 5;
         uint32_t acc;
         if (c == 1024u) {
             // the words of a half wave lie in one batch (the stride is a
-            // multiple of 64 words); a wave's last words may be past the end,
-            // so the lanes that hold hashes are those that loop
+            // multiple of 64 words); in the last, partial wave a lane that
+            // would hold a hash may have no word and not loop, so every lane
+            // hashes for itself there
             const uint64_t b = w >> 5;
             const uint32_t ow = (uint32_t)w & 31u;
             const BloomHash mine = bloom_hash(seed, k, brows, cmask, b, ow);
@@ -2813,8 +2819,6 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ea.last_mask = last_mask;
         ea.x_vec = x_vec;
         ea.mask_vec = mask_vec;
-        ea.fill = fill_groups != 0 ? &sync->fill.v[0] : nullptr;
-        ea.mask_chunks = pa.mask_chunks;
         ea.b_vec = bvec;
         // Chunks are shared until the grid reaches the eight workgroups that fit
         // on a CU: with fewer they are all in flight at once and the time is one
