@@ -70,6 +70,12 @@ def test_filled_decode_matches(n, kind, vtype):
             if "coo_idx" in o:
                 assert torch.equal(o["coo_idx"].long(), torch.nonzero(x).reshape(-1))
                 assert torch.equal(o["coo_val"], x[x != 0])
+        whole, winf = _decode(hc, p, y, b, n, ["x", "mask", "coo"], plan)  # written whole
+        tight, inf = _decode(hc, p, y, b, m, ["x", "mask", "coo"], plan)
+        assert winf == inf
+        assert torch.equal(whole["x_out"], tight["x_out"]) and torch.equal(whole["mask"], tight["mask"])
+        for k in ("coo_idx", "coo_val"):
+            assert torch.equal(whole[k][:m], tight[k])
 
 
 @pytest.mark.parametrize("gamma,short", [(1.0, 0), (1.35, 1)])

@@ -14,6 +14,10 @@ pytestmark = pytest.mark.gpu
     (1 << 27, (1 << 26) + 1, True),   # counters and residuals apart
     (3_000_001, 60_000, True),        # half the CUs
     (3_000_001, 60_000, False),
+    (20_000_001, 1_390_000, True),    # just under 2^21 cells: half the CUs
+    (20_000_001, 1_400_000, True),    # 2^21 to 2^23 cells: three quarters
+    (40_000_003, 5_500_000, True),
+    (40_000_003, 5_500_000, False),
     (40_000_003, 8_000_000, True),    # round 0 over the whole chip
     (40_000_003, 8_000_000, False),
 ])

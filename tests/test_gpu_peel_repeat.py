@@ -7,8 +7,8 @@ the recovered set, the values or the round count.  Every one of many decodes
 of the same aggregate must therefore equal the oracle's (int32, bit-exact,
 rounds included) or the first decode (fp32: the smallest-j rule makes the
 decode independent of the order of the entries, so repeats are bit-identical).
-Sizes: a sketch peeled on half the CUs with round 0 in the peel kernel, and a
-full-size VGG19-shaped sketch peeled on three quarters of the CUs after round
+Sizes: a sketch peeled on half the CUs with round 0 in the peel kernel, an fp32
+one on three quarters of them, and a full-size VGG19-shaped sketch peeled on three quarters of the CUs after round
 0 by rows."""
 import numpy as np
 import pytest
@@ -61,15 +61,17 @@ def _decodes(hc, p, Ya, Ba, plan, max_support, reps):
         yield k, out.cpu().numpy(), mask.cpu().numpy(), hc.read_info(info)
 
 
-@pytest.mark.parametrize("kind", ["i32_plan", "i32_noplan", "f32_plan"])
+@pytest.mark.parametrize("kind", ["i32_plan", "i32_noplan", "f32_plan", "f32_wide_plan"])
 def test_peel_repeat_half_grid(kind):
     import torch
     hc = _hc()
     vt = "f32" if kind.startswith("f32") else "i32"
-    w = wl.make("synthetic", n=6_000_011, W=4, density=0.01, overlap=0.5, data_seed=77,
-                vtype=vt)
+    wide = "wide" in kind  # over 2^21 cells: three quarters of the CUs for fp32
+    w = wl.make("synthetic", n=24_000_011 if wide else 6_000_011, W=4,
+                density=0.03 if wide else 0.01, overlap=0.5, data_seed=77, vtype=vt)
     p = hc.hc_geometry(w.n, w.n_agg, hc.GAMMA, 1024, w.hash_seed, vt)
     plan = hc.make_plan(p, torch.device("cuda")) if kind.endswith("_plan") else None
+    assert (p.cells >= 1 << 21) == wide
     Ya, Ba = _aggregate(hc, w, p)
     print(f"[peel repeat] {kind} n={w.n} cells={p.cells} support={w.n_agg}", flush=True)
     if vt == "i32":

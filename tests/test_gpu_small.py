@@ -27,12 +27,17 @@ def _w(n, vtype="i32", W=3, density=0.01):
     (1024, 3, 1024), (1025, 3, 1024), (65536 + 7, 5, 1024), (1024 * 1024, 14, 1024),
     (1024 * 1024, 15, 1024), (1024 * 1024 + 1, 14, 1024), (700 * 1024 + 33, 9, 1024),
     (512 * 1024, 28, 512), (256 * 1024, 56, 256), (256 * 1024 + 1, 40, 256), (1024 * 32, 100, 32),
+    (640 * 1024, 15, 1024), (640 * 1024 + 1, 15, 1024),  # 15 rows fit beside 640 batches
 ])
 def test_small_int32(n, rows, c):
     check_int(_w(n, density=min(0.3, 0.25 * rows * c / n)), rows, c, use_plan=c >= 256)
 
 
-@pytest.mark.parametrize("n,rows", [(300 * 1024 + 5, 10), (300 * 1024 + 5, 11), (1024 * 1024, 9)])
+# fp32: 10 rows fit beside 1024 batches, 11 beside 347
+@pytest.mark.parametrize("n,rows", [
+    (300 * 1024 + 5, 10), (300 * 1024 + 5, 11), (1024 * 1024, 9), (1024 * 1024, 10),
+    (1024 * 1024, 11), (300 * 1024 + 5, 12), (347 * 1024, 11), (347 * 1024 + 1, 11),
+])
 def test_small_fp32(n, rows):
     check_fp32(_w(n, "f32", density=min(0.3, 0.25 * rows * 1024 / n)), rows, 1024)
 
