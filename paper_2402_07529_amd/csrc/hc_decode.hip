@@ -71,26 +71,27 @@ constexpr uint32_t kPeelPushCap = 8 * kPeelBlock;  // staged frontier entries pe
 constexpr uint64_t kPeelHalfGridCells = 8ull << 20;  // below this many cells the peel uses half the CUs
 constexpr uint64_t kPeelMostGridCellsF32 = 2ull << 20;  // fp32: three quarters from here to that bound
 constexpr uint64_t kPeelHalfGridCellsInt = 32ull << 20;  // the same with residuals in the counters
-constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a counter (count_bits = 32)
+constexpr unsigned long long kOne = 1ull << 32;  // one incidence in a packed counter
 
-// The fp32 decode keeps each cell's counter and fp64 residual side by side in
-// one 16-byte record: counter i is 64-bit word 2 i and its residual word
-// 2 i + 1.  The int32 decode keeps two arrays.
-template <bool F32> constexpr uint32_t kCounterStride = F32 ? 2u : 1u;
-template <typename T> constexpr uint32_t kCellStride = kCounterStride<std::is_same<T, double>::value>;
-// With at most 2^kPairBits support elements the fp32 peel holds the counters
-// as doubles, deg * 2^kPairBits + (sum of positions) < 2^53, always exact (see
-// peel_pairs).  They are built in that form as 64-bit integers: from counters
-// of deg * 2^32 + sum the two could not be told apart where the sum passes
-// 2^32.
-constexpr uint32_t kPairBits = 26;
-
-// Bits below the degree in the counters as they are built.  (Constant for
-// int32: read from a register, the counter kernel's adds cost 1 % of a decode
-// of 60 M parameters.)
-template <bool F32> __device__ __forceinline__ uint32_t count_bits(uint64_t nsup) {
-    return F32 && nsup <= (1ull << kPairBits) ? kPairBits : 32u;
-}
+// The fp32 decode keeps a cell's counter and fp64 residual side by side as
+// doubles in one 16-byte record (a pair: counter i is 64-bit word 2 i, its
+// residual word 2 i + 1) for supports of at most `most` elements, otherwise,
+// as the int32 decode, in two arrays, the counters as 64-bit integers.  In a
+// pair the counter is deg * 2^bits + (sum of positions): most <= 2^bits, and a
+// cell has at most an element of every batch (and of the support), so that
+// batches * 2^(bits + 1) <= 2^53 (or bits = 26) keeps it and every update
+// exact.  It is built in that form: from counters of deg * 2^32 + sum the two
+// could not be told apart where the sum passes 2^32.
+struct Pairs {
+    uint64_t most;                // 0: none (and for int32)
+    uint64_t skip_from, skip_to;  // nor for supports in this range
+    uint32_t bits;
+    __host__ __device__ bool at(uint64_t nsup) const {
+        return most != 0 && nsup <= most && (nsup < skip_from || nsup > skip_to);
+    }
+    // One incidence in a counter as it is built.
+    __host__ __device__ unsigned long long one(bool pair) const { return 1ull << (pair ? bits : 32u); }
+};
 
 // The int32 peel can carry a cell's residual in its counter word: value in
 // the high 32 bits, deg * 2^k + (sum of member positions) in the low 32, with
@@ -166,13 +167,17 @@ template <typename T>
 __device__ __forceinline__ void prep_cells(const T* __restrict__ y_agg,
                                            typename Acc<T>::type* __restrict__ yw,
                                            unsigned long long* __restrict__ cnt, uint32_t cells,
-                                           bool planned, bool zero_cnt,
+                                           bool planned, bool zero_cnt, bool pair,
                                            uint32_t* __restrict__ mark, uint64_t first,
                                            uint64_t step) {
     for (uint64_t i = first; i < cells; i += step) {
         if constexpr (std::is_same<T, float>::value) {
-            // one 16-byte store per record
-            reinterpret_cast<double2*>(cnt)[i] = make_double2(0.0, (double)y_agg[i]);
+            if (pair) {  // one 16-byte store per record
+                reinterpret_cast<double2*>(cnt)[i] = make_double2(0.0, (double)y_agg[i]);
+            } else {
+                yw[i] = (double)y_agg[i];
+                if (zero_cnt) cnt[i] = 0ull;
+            }
             mark[i] = 0u;
         } else {
             if (!planned) yw[i] = y_agg[i];
@@ -181,20 +186,17 @@ __device__ __forceinline__ void prep_cells(const T* __restrict__ y_agg,
     }
 }
 
+// small: the support size is not known yet (support_small_kernel counts it)
 template <typename T>
 __global__ __launch_bounds__(kBlock) void prep_kernel(const T* __restrict__ y_agg,
                                                       typename Acc<T>::type* __restrict__ yw,
                                                       unsigned long long* __restrict__ cnt,
                                                       uint32_t cells, bool planned, bool zero_cnt,
-                                                      Ctrl* __restrict__ ctrl,
-                                                      PeelSync* __restrict__ sync,
+                                                      const Ctrl* __restrict__ ctrl, bool small,
+                                                      Pairs pairs,
                                                       uint32_t* __restrict__ mark) {
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[threadIdx.x] = 0u;
-        for (uint32_t k = threadIdx.x; k < sizeof(PeelSync) / 4; k += kBlock)
-            reinterpret_cast<uint32_t*>(sync)[k] = 0u;
-    }
-    prep_cells<T>(y_agg, yw, cnt, cells, planned, zero_cnt, mark,
+    const bool pair = std::is_same<T, float>::value && pairs.at(small ? 0 : ctrl->n_support);
+    prep_cells<T>(y_agg, yw, cnt, cells, planned, zero_cnt, pair, mark,
                   (uint64_t)blockIdx.x * kBlock + threadIdx.x, (uint64_t)gridDim.x * kBlock);
 }
 
@@ -310,7 +312,14 @@ __global__ __launch_bounds__(kBlock) void tile_count_kernel(const uint32_t* __re
                                                             uint64_t words, uint32_t last_mask,
                                                             bool vec, uint64_t nchunks,
                                                             uint32_t* __restrict__ cpre,
-                                                            uint32_t* __restrict__ tcnt) {
+                                                            uint32_t* __restrict__ tcnt,
+                                                            Ctrl* __restrict__ ctrl,
+                                                            PeelSync* __restrict__ sync) {
+    if (blockIdx.x == 0) {  // the decode's control words, before the scan writes some
+        if (threadIdx.x < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(ctrl)[threadIdx.x] = 0u;
+        for (uint32_t k = threadIdx.x; k < sizeof(PeelSync) / 4; k += kBlock)
+            reinterpret_cast<uint32_t*>(sync)[k] = 0u;
+    }
     __shared__ uint32_t s_cnt[kBlock / 64][kTileChunks];
     const uint32_t lane = lane_id();
     const uint32_t wave = threadIdx.x >> 6;
@@ -355,25 +364,25 @@ struct SupportArgs {
     Ctrl* ctrl;
     uint64_t words, nchunks, cap, seed;
     uint32_t last_mask, log2wpb, nb, rows, c, cmask, log2c;
-    uint32_t cstride;            // 64-bit words from one counter to the next
+    Pairs pairs;
     bool vec;  // b is 16-byte aligned
 };
 
 // Element pos of E is parameter p: its list entry, its cleared flag and,
-// without a plan, its three counter increments (one: an incidence).  Positions
-// past the capacity are dropped (the decode then reports overflow).
+// without a plan, its three counter increments.  Positions past the capacity
+// are dropped (the decode then reports overflow).
 __device__ __forceinline__ void support_put(const SupportArgs& a, uint32_t pos, uint32_t p,
-                                            unsigned long long one) {
+                                            bool pair) {
     if (pos >= a.cap) return;
     a.elem[pos] = p;
     a.peeled[pos] = 0u;
     if (a.woffb == nullptr) {
         const BatchHash h = batch_hash(a.seed, a.rows, a.cmask, p >> a.log2c);
         const uint32_t t = p & a.cmask;
-        const unsigned long long inc = one + pos;
+        const unsigned long long inc = a.pairs.one(pair) + pos;
 #pragma unroll
         for (int j = 0; j < 3; j++)
-            atomicAdd(a.cnt + (uint64_t)a.cstride * cell_of(h, j, t, a.c, a.cmask), inc);
+            atomicAdd(a.cnt + ((uint64_t)cell_of(h, j, t, a.c, a.cmask) << (pair ? 1 : 0)), inc);
     }
 }
 
@@ -383,12 +392,12 @@ constexpr uint32_t kWaveStage = 1024;  // elements one wave stages in LDS at a t
 // consecutive elements.  Every lane has written its stage entries.
 __device__ __forceinline__ void support_flush(const SupportArgs& a, uint32_t* stage,
                                               uint32_t total, uint32_t base, uint32_t lane,
-                                              unsigned long long one) {
+                                              bool pair) {
     if (total == 0) return;
     // the wave's LDS writes are complete before any lane reads them back
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
-    for (uint32_t j = lane; j < total; j += 64) support_put(a, base + j, stage[j], one);
+    for (uint32_t j = lane; j < total; j += 64) support_put(a, base + j, stage[j], pair);
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();  // the stage is refilled next
 }
@@ -414,7 +423,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
     uint32_t base = a.toff[chunk / kTileChunks] + a.cpre[chunk];
     if (lane == 0) a.blk[chunk] = base;
     const uint64_t wmask = (1ull << a.log2wpb) - 1ull;
-    const unsigned long long one = 1ull << (a.cstride == 2u ? count_bits<true>(a.ctrl->n_support) : 32u);
+    const bool pair = a.pairs.at(a.ctrl->n_support);
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const uint32_t w4[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -443,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
             if (!staged) o += __popc(w4[k]);
         }
         if (staged) {
-            support_flush(a, stage, total, base, lane, one);
+            support_flush(a, stage, total, base, lane, pair);
         } else {
             // over 1/8 dense: eight passes of 32 words, two lanes per word
             // (16 bits each), at most 1024 elements a pass
@@ -465,7 +474,7 @@ __global__ __launch_bounds__(kBlock) void support_kernel(SupportArgs a) {
                     stage[q++] = (uint32_t)(w * 32u) + 16u * half + (uint32_t)__builtin_ctz(bits);
                     bits &= bits - 1u;
                 }
-                support_flush(a, stage, ptotal, pbase, lane, one);
+                support_flush(a, stage, ptotal, pbase, lane, pair);
                 pbase += ptotal;
             }
         }
@@ -494,7 +503,7 @@ __global__ __launch_bounds__(kSupportBlock) void support_small_kernel(
     const uint32_t tid = threadIdx.x;
     const uint32_t nchunks = (uint32_t)a.nchunks;
     if (blockIdx.x >= nchunks) {
-        prep_cells<T>(y_agg, yw, a.cnt, cells, true, zero_cnt, mark,
+        prep_cells<T>(y_agg, yw, a.cnt, cells, true, zero_cnt, a.pairs.at(0), mark,
                       (uint64_t)(blockIdx.x - nchunks) * kSupportBlock + tid,
                       (uint64_t)(gridDim.x - nchunks) * kSupportBlock);
         return;
@@ -522,10 +531,9 @@ __global__ __launch_bounds__(kSupportBlock) void support_small_kernel(
         a.woffb[w >> a.log2wpb] = base + excl;
     const uint32_t wave = uniform(tid >> 6);
     const uint32_t wbase = base + uniform(excl);  // lane 0's rank: the wave's first
-    static_assert(kSmallChunks * kChunkBits <= (1ull << kPairBits), "count_bits without |S|");
-    const unsigned long long one = 1ull << (a.cstride == 2u ? count_bits<true>(0) : 32u);
+    const bool pair = a.pairs.at(0);
     for_each_set_bit(word, [&](uint32_t s, bool valid, uint32_t owner, uint32_t bit) {
-        if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit, one);
+        if (valid) support_put(a, wbase + s, (c0 + 64u * wave + owner) * 32u + bit, pair);
     });
     if (blockIdx.x == nchunks - 1u) {
         if (tid < sizeof(Ctrl) / 4) reinterpret_cast<uint32_t*>(a.ctrl)[tid] = 0u;
@@ -645,6 +653,7 @@ struct CounterArgs {
     Ctrl* ctrl;
     uint64_t n, seed, words, nb;
     uint32_t rows, c, cmask, cells, last_mask;
+    Pairs pairs;
     uint32_t split;    // counter_kernel: workgroups sharing a row's entries
 };
 
@@ -652,7 +661,7 @@ struct CounterArgs {
 // each taking a run of its plan entries.  Cell k of row r gathers, from
 // every (batch b, hash j) in the row's plan entry list, the parameter
 // t = (k - bias_j(b)) mod c of batch b: if its bit is set it adds an incidence
-// (2^count_bits) + its rank in the support.  Integer sums, so the result equals the atomic build
+// + its rank in the support.  Integer sums, so the result equals the atomic build
 // exactly whatever the order.  Every step issues its global loads together,
 // so a row costs a few memory latencies however many batches land on it:
 //   screen  each lane takes one plan entry (kBlock at a time) and checks
@@ -696,7 +705,10 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         return;
     }
     if (overflow) return;
-    const unsigned long long one = 1ull << count_bits<F32>(nsup);
+    // (constants for int32: from a register, the adds cost 1 % of a decode)
+    const bool pair = F32 && a.pairs.at(nsup);
+    const unsigned long long one = F32 ? a.pairs.one(pair) : kOne;
+    const uint32_t stride = pair ? 2u : 1u;  // 64-bit words from one counter to the next
     const uint32_t kpack = pack_bits(nsup);
     uint32_t row = part / a.split;
     uint32_t r0 = a.rowoff[row], r1 = a.rowoff[row + 1];
@@ -758,7 +770,7 @@ __global__ __launch_bounds__(kBlock) void counter_kernel(CounterArgs a) {
         bool fits = true;
         for (uint32_t k = threadIdx.x; k < C; k += kBlock) {
             const unsigned long long acc = s_acc[k];
-            unsigned long long* const dst = a.cnt + (uint64_t)kCounterStride<F32> * (row * C + k);
+            unsigned long long* const dst = a.cnt + (uint64_t)stride * (row * C + k);
             if (a.split == 1u) *dst = acc;
             else if (acc != 0ull) atomicAdd(dst, acc);
             fits = fits && (F32 || fits_packed_share(acc, kpack, a.split));
@@ -794,7 +806,10 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
     }
     if (a.ctrl->overflow) return;
     const unsigned long long nsup = a.ctrl->n_support;
-    const unsigned long long one = 1ull << count_bits<F32>(nsup);
+    // (constants for int32: from a register, the adds cost 1 % of a decode)
+    const bool pair = F32 && a.pairs.at(nsup);
+    const unsigned long long one = F32 ? a.pairs.one(pair) : kOne;
+    const uint32_t stride = pair ? 2u : 1u;  // 64-bit words from one counter to the next
     const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
@@ -840,12 +855,12 @@ __global__ __launch_bounds__(kBlock) void counter_wave_kernel(CounterArgs a) {
                 }
             }
         }
-        unsigned long long* dst = a.cnt + (uint64_t)row * C * kCounterStride<F32>;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * stride;
         bool fits = true;
 #pragma unroll
         for (uint32_t i = 0; i < CPL; i++) {
             const unsigned long long v = acc[i * 64u + lane];
-            dst[kCounterStride<F32> * (i * 64u + lane)] = v;
+            dst[stride * (i * 64u + lane)] = v;
             fits = fits && (F32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
@@ -1059,7 +1074,10 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     if (!plan_matches(a)) return;
     if (a.ctrl->overflow) return;
     const unsigned long long nsup = a.ctrl->n_support;
-    const unsigned long long one = 1ull << count_bits<F32>(nsup);
+    // (constants for int32: from a register, the adds cost 1 % of a decode)
+    const bool pair = F32 && a.pairs.at(nsup);
+    const unsigned long long one = F32 ? a.pairs.one(pair) : kOne;
+    const uint32_t stride = pair ? 2u : 1u;  // 64-bit words from one counter to the next
     const uint32_t kpack = pack_bits(nsup);
     const uint32_t lane = lane_id();
     const uint32_t wave = uniform(threadIdx.x >> 6);
@@ -1067,11 +1085,11 @@ __global__ __launch_bounds__(kBlock) void counter_rows_kernel(CounterArgs a) {
     const uint32_t nwaves = gridDim.x * kWaves;
     for (uint32_t row = blockIdx.x * kWaves + wave; row < a.rows; row += nwaves) {
         build_row<C, false>(a, row, acc, one);
-        unsigned long long* dst = a.cnt + (uint64_t)row * C * kCounterStride<F32>;
+        unsigned long long* dst = a.cnt + (uint64_t)row * C * stride;
         bool fits = true;
         for (uint32_t k = lane; k < (uint32_t)C; k += 64) {
             const unsigned long long v = acc[k];
-            dst[kCounterStride<F32> * k] = v;
+            dst[stride * k] = v;
             fits = fits && (F32 || fits_packed(v, kpack));
         }
         flag_unpackable(a.ctrl, fits);
@@ -1540,6 +1558,7 @@ struct PeelArgs {  // T: the decode-side arithmetic type
     uint32_t rows, c, cmask, log2c, cells;
     bool counted;   // a counter kernel built the counters (and checked their packing)
     bool split0;    // round 0 ran before the peel kernel, as whole-chip launches
+    Pairs pairs;
     uint32_t row_launches;  // further rounds launched by rows, of which rows_rounds ran if the
     uint64_t n;             // counters pack
     // the workgroups from peel_groups on zero the dense outputs while the
@@ -1566,33 +1585,41 @@ __device__ __forceinline__ void scan_residual(const PeelArgs<T>& a, uint64_t cid
         else
             __hip_atomic_store(a.yw + cidx, (int32_t)y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
-        // fp32: the residual is in the record already; the counter, built with
-        // kPairBits (kp) below the degree, becomes a double
+        // fp32: the residual is in the pair already; the counter becomes a double
         if (!packed || cidx >= a.cells) return;
         st_agent64(a.cnt + 2 * cidx, __builtin_bit_cast(unsigned long long, (double)v));
     }
 }
 
 // Bits below the degree in the fused form's counters.
-template <typename T> __device__ __forceinline__ uint32_t peel_bits(uint64_t nsup) {
-    return std::is_same<T, int32_t>::value ? pack_bits(nsup) : kPairBits;
+template <typename T>
+__device__ __forceinline__ uint32_t peel_bits(const PeelArgs<T>& a, uint64_t nsup) {
+    return std::is_same<T, int32_t>::value ? pack_bits(nsup) : a.pairs.bits;
 }
 // Whether the peel runs its fused form: int32 with the residuals in the
-// counter words, or fp32 with the counters as doubles.
+// counter words, or fp32 with counters and residuals in pairs.
 template <typename T>
 __device__ __forceinline__ bool peel_packed(const PeelArgs<T>& a, uint64_t nsup) {
     if constexpr (std::is_same<T, int32_t>::value) return a.counted && a.ctrl->nopack == 0;
-    return count_bits<true>(nsup) == kPairBits;
+    return a.pairs.at(nsup);
 }
 // Bits below the degree in the counters that the round-0 scan reads.
-template <typename T> __device__ __forceinline__ uint32_t scan_bits(bool packed) {
-    return !std::is_same<T, int32_t>::value && packed ? kPairBits : 32u;
+template <typename T>
+__device__ __forceinline__ uint32_t scan_bits(const PeelArgs<T>& a, bool packed) {
+    return !std::is_same<T, int32_t>::value && packed ? a.pairs.bits : 32u;
+}
+// The 64-bit word of a cell's counter, and an fp32 pair's residual.
+template <typename T> __device__ __forceinline__ uint64_t counter_word(uint64_t cidx, bool packed) {
+    return !std::is_same<T, int32_t>::value && packed ? 2u * cidx : cidx;
+}
+__device__ __forceinline__ double* pair_residual(const PeelArgs<double>& a, uint64_t cidx) {
+    return reinterpret_cast<double*>(a.cnt) + 2u * cidx + 1u;
 }
 
 // One frontier entry (cell cidx, element position pos): whether it recovers
 // its element this round, and then the element's value (written), its two
 // other cells oc and the bits of oneg: the signs g of the element in them.
-// PACKED (int32): residuals ride in the counter words.
+// PACKED: int32 residuals ride in the counter words, fp32 ones sit in pairs.
 // Integer peels (T = int32): the first frontier entry of an element to claim
 // its flag recovers it; any of its pure cells holds the same value exactly.
 // The fp32 gradient's peel (T = double, with marks): every element is
@@ -1625,9 +1652,11 @@ __device__ __forceinline__ bool peel_decide(const PeelArgs<T>& a, uint32_t cidx,
     // the compiler had hoisted above their differing loads)
     unsigned long long wcell = 0;
     T ycell = T(0);
-    if (PACKED) wcell = ld_agent64(a.cnt + cidx);
-    else ycell = __hip_atomic_load(a.yw + (uint64_t)kCellStride<T> * cidx, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (kMarks)
+        ycell = __hip_atomic_load(PACKED ? pair_residual(a, cidx) : a.yw + cidx, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+    else if (PACKED) wcell = ld_agent64(a.cnt + cidx);
+    else ycell = __hip_atomic_load(a.yw + cidx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool taken;
     if (kMarks)
         taken = (__hip_atomic_load(fword, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & fbit) != 0u;
@@ -1642,7 +1671,7 @@ __device__ __forceinline__ bool peel_decide(const PeelArgs<T>& a, uint32_t cidx,
     const int j = cl[0] == cidx ? 0 : (cl[1] == cidx ? 1 : 2);
     // the cell's load stays beside the claim's and the element's: otherwise
     // the compiler sinks it past the test below, a memory latency later
-    if (PACKED) {
+    if (PACKED && !kMarks) {
         const uint32_t hi = (uint32_t)(wcell >> 32);
         asm volatile("" : : "v"(hi));
     } else {
@@ -1656,7 +1685,7 @@ __device__ __forceinline__ bool peel_decide(const PeelArgs<T>& a, uint32_t cidx,
                 return false;
         __hip_atomic_store(a.peeled + pos, (uint8_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (PACKED) ycell = (T)(int32_t)(uint32_t)(wcell >> 32);
+    if (PACKED && !kMarks) ycell = (T)(int32_t)(uint32_t)(wcell >> 32);
     val = Val<T>::sign(ycell, (h.neg >> j) & 1u);
     a.vals[pos] = val;
     const int jo[2] = {j == 0 ? 1 : 0, j == 2 ? 1 : 2};
@@ -1734,8 +1763,8 @@ __device__ __forceinline__ bool peel_entry(const PeelArgs<T>& a, uint2 it, uint3
             inc[u] = ((unsigned long long)(uint32_t)(int32_t)gx << 32) - ((1ull << kp) + it.y);
         else
             inc[u] = 0ull - (kOne + it.y);
-        old[u] = atomicAdd(a.cnt + (uint64_t)kCellStride<T> * oc[u], inc[u]);
-        if (!PACKED) Val<T>::atomic_add(a.yw + (uint64_t)kCellStride<T> * oc[u], gx);
+        old[u] = atomicAdd(a.cnt + oc[u], inc[u]);
+        if (!PACKED) Val<T>::atomic_add(a.yw + oc[u], gx);
     }
 #pragma unroll
     for (int u = 0; u < 2; u++) {
@@ -1769,7 +1798,7 @@ __device__ __forceinline__ void peel_step(const PeelArgs<T>& a, bool have, uint2
     } else if (packed) {
         T val = T(0);
         uint32_t oneg = 0;
-        if (have) act = peel_decide<T, false>(a, it.x, it.y, r, val, oc, oneg);
+        if (have) act = peel_decide<T, true>(a, it.x, it.y, r, val, oc, oneg);
         peel_pairs(a, act, it.y, val, oc, oneg, kp, q);
     } else if (have) {
         act = peel_entry<T, false>(a, it, kp, r, push, oc, ppos);
@@ -1923,10 +1952,10 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 
     if (!skip) {
         const uint32_t nsup = (uint32_t)ctrl->n_support;
-        const uint32_t kp = peel_bits<T>(nsup);
+        const uint32_t kp = peel_bits(a, nsup);
         const bool packed = peel_packed(a, nsup);
         if (!a.split0) {
-            const uint32_t sb = scan_bits<T>(packed);
+            const uint32_t sb = scan_bits(a, packed);
             // round 0's frontier is every cell with exactly one element;
             // packed, each counter also takes its cell's residual in its high
             // word.  Four cells per lane and pass, loaded together, then staged.
@@ -1938,7 +1967,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_kernel(PeelArgs<T> a) {
 #pragma unroll
                 for (uint32_t m = 0; m < kScanCells; m++) {
                     const uint64_t cidx = base + m * nthreads + gtid;
-                    v[m] = cidx < a.cells ? a.cnt[kCellStride<T> * cidx] : 0ull;
+                    v[m] = cidx < a.cells ? a.cnt[counter_word<T>(cidx, packed)] : 0ull;
                 }
 #pragma unroll
                 for (uint32_t m = 0; m < kScanCells; m++) {
@@ -2053,9 +2082,9 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
     if (threadIdx.x == 0) q.count = 0;
     lds_barrier();
     const uint32_t nsup = (uint32_t)ctrl->n_support;
-    const uint32_t kp = peel_bits<T>(nsup);
+    const uint32_t kp = peel_bits(a, nsup);
     const bool packed = peel_packed(a, nsup);
-    const uint32_t sb = scan_bits<T>(packed);
+    const uint32_t sb = scan_bits(a, packed);
     const uint64_t nthreads = (uint64_t)gridDim.x * kBlock;
     const uint64_t gtid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     for (uint64_t base = 0; base < a.cells; base += kScanCells * nthreads) {
@@ -2063,7 +2092,7 @@ __global__ __launch_bounds__(kBlock) void scan0_kernel(PeelArgs<T> a) {
 #pragma unroll
         for (uint32_t m = 0; m < kScanCells; m++) {
             const uint64_t cidx = base + m * nthreads + gtid;
-            v[m] = cidx < a.cells ? a.cnt[kCellStride<T> * cidx] : 0ull;
+            v[m] = cidx < a.cells ? a.cnt[counter_word<T>(cidx, packed)] : 0ull;
         }
 #pragma unroll
         for (uint32_t m = 0; m < kScanCells; m++) {
@@ -2094,7 +2123,7 @@ __global__ __launch_bounds__(kBlock) void round0_kernel(PeelArgs<T> a) {
     }
     lds_barrier();
     const uint32_t nsup = (uint32_t)ctrl->n_support;
-    const uint32_t kp = peel_bits<T>(nsup);
+    const uint32_t kp = peel_bits(a, nsup);
     const bool packed = peel_packed(a, nsup);
     uint32_t qe = a.sync->round0.v[0];
     if (qe > a.cells) qe = a.cells;
@@ -2141,7 +2170,7 @@ __global__ __launch_bounds__(kBlock) void leftover_kernel(PeelArgs<T> a) {
     if (ctrl->overflow != 0 || ctrl->bad_plan != 0) return;
     const uint32_t nsup = (uint32_t)ctrl->n_support;
     // the same test as the peel kernel's
-    const bool packed = std::is_same<T, int32_t>::value && a.counted && ctrl->nopack == 0;
+    const bool packed = peel_packed(a, nsup);
     const uint32_t stride = gridDim.x * kBlock;
     for (uint32_t pos = blockIdx.x * kBlock + threadIdx.x; pos < nsup; pos += stride) {
         if (a.peeled[pos]) continue;
@@ -2152,8 +2181,11 @@ __global__ __launch_bounds__(kBlock) void leftover_kernel(PeelArgs<T> a) {
 #pragma unroll
         for (int j = 0; j < 3; j++) {
             const uint32_t cell = cell_of(h, j, t, a.c, a.cmask);
-            const T y = packed ? (T)(int32_t)(uint32_t)(a.cnt[cell] >> 32)
-                               : a.yw[(uint64_t)kCellStride<T> * cell];
+            T y;
+            if constexpr (std::is_same<T, int32_t>::value)
+                y = packed ? (int32_t)(uint32_t)(a.cnt[cell] >> 32) : a.yw[cell];
+            else
+                y = packed ? *pair_residual(a, cell) : a.yw[cell];
             e3[j] = Val<T>::sign(y, (h.neg >> j) & 1u);
         }
         a.vals[pos] = median3(e3[0], e3[1], e3[2]);
@@ -2479,6 +2511,30 @@ __global__ __launch_bounds__(kBlock) void bloom_probe_kernel(
     }
 }
 
+// Which supports an fp32 decode keeps as pairs.  They pay where the sketch can
+// peel, from 1.2 cells per element (60 M parameters, 10 % dense, with a plan,
+// two arrays and pairs: 0.15 cells 286 and 371 us, 0.8 499 and 547, 1.0 705 and
+// 701, 1.25 2081 and 1451): below that most elements are left, and pairs only
+// spread the counters' and the estimates' loads over twice the lines.  Nor do
+// they for dense supports in wide sketches, which peel in a few rounds over
+// whole lines: from 0.4 of the parameters in 2.2 cells each (143.7 M
+// parameters, 69.6 %: 1.5 cells 28.2 and 24.5 ms, 2.2 20.3 and 20.5, 2.6 18.3
+// and 19.5), or 2 without a plan, where the counters are added by atomics
+// (80 M, 50 %: 1.5 cells 13.0 and 11.9, 2.2 11.0 and 11.2, 2.9 9.8 and 10.8).
+Pairs choose_pairs(const Geo& g, const DecodeLayout& L, bool planned) {
+    if (!g.f32) return {0, 0, 0, 32u};
+    const uint64_t nb = (g.n + g.c - 1) / g.c;
+    uint32_t bits = 31;  // a support is below 2^31
+    while (bits > 26u && nb > 1ull << (52u - bits)) bits--;
+    const uint64_t most = 1ull << bits;
+    // a short bitmap's kernels choose before the support is counted
+    static_assert(kSmallChunks * kChunkBits <= 1ull << 26, "pairs fit any of their supports");
+    if (L.nchunks <= kSmallChunks)
+        return {L.cap == g.n || 2ull * g.cells >= L.cap ? most : 0, 1, 0, bits};
+    return {std::min<uint64_t>(most, 5ull * g.cells / 6), std::max<uint64_t>(2 * g.n / 5, 1),
+            planned ? 5ull * g.cells / 11 : g.cells / 2, bits};
+}
+
 template <typename T>
 hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
                            const uint32_t* b, const DecodeOut& out, const DecodeLayout& L,
@@ -2495,8 +2551,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     A* vals = reinterpret_cast<A*>(base + L.vals);
     uint8_t* peeled = reinterpret_cast<uint8_t*>(base + L.peeled);
     unsigned long long* cnt = reinterpret_cast<unsigned long long*>(base + L.cnt);
-    // fp32: {counter, residual} records over the two arrays' room
-    A* yw = g.f32 ? reinterpret_cast<A*>(base + L.cnt) + 1 : reinterpret_cast<A*>(base + L.yw);
+    A* yw = reinterpret_cast<A*>(base + L.yw);  // fp32 pairs: records over cnt and yw
     uint2* queue = reinterpret_cast<uint2*>(base + L.queue);
     uint32_t* mark = g.f32 ? reinterpret_cast<uint32_t*>(base + L.mark) : nullptr;
     const T* y_agg = static_cast<const T*>(y_agg_v);
@@ -2546,19 +2601,21 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     sa.c = g.c;
     sa.cmask = g.cmask;
     sa.log2c = g.log2c;
-    sa.cstride = kCellStride<A>;
+    const Pairs pairs = choose_pairs(g, L, planned);
+    sa.pairs = pairs;
     sa.vec = bvec;
     // the support offsets and lists, and the cells' initial state
     const bool small = L.nchunks <= kSmallChunks;
-    if (!planned || !small) {
+    auto prep = [&]() {
         const uint64_t cap = (uint64_t)di.cus * 16;
         const uint32_t grid = (uint32_t)(cell_groups < cap ? cell_groups : cap);
         hipLaunchKernelGGL(prep_kernel<T>, dim3(grid), dim3(kBlock), 0, s, y_agg, yw, cnt,
-                           g.cells, planned, zero_cnt, ctrl, sync, mark);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+                           g.cells, planned, zero_cnt, ctrl, small, pairs, mark);
+        return hipGetLastError();
+    };
     if (small) {
-        // the cells' preparation rides along where nothing in this launch needs it
+        if (!planned && (e = prep()) != hipSuccess) return e;
+        // with a plan the cells' preparation rides along: nothing in this launch needs it
         uint32_t extra = 0;
         if (planned && (g.f32 || zero_cnt))
             extra = (uint32_t)std::min<uint64_t>((g.cells + kSupportBlock - 1) / kSupportBlock,
@@ -2568,10 +2625,11 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         hipLaunchKernelGGL(tile_count_kernel, dim3((uint32_t)L.ntiles), dim3(kBlock), 0, s, b,
-                           g.words, last_mask, bvec, L.nchunks, cpre, tcnt);
+                           g.words, last_mask, bvec, L.nchunks, cpre, tcnt, ctrl, sync);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, tcnt, L.ntiles, ctrl, L.cap);
         if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = prep()) != hipSuccess) return e;  // its form depends on the support size
         hipLaunchKernelGGL(support_kernel,
                            dim3((uint32_t)((L.nchunks + kBlock / 64 - 1) / (kBlock / 64))),
                            dim3(kBlock), 0, s, sa);
@@ -2652,6 +2710,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
         ca.cmask = g.cmask;
         ca.cells = g.cells;
         ca.last_mask = last_mask;
+        ca.pairs = pairs;
         ca.split = split;
         // Rows to spare (two or more per SIMD): one wave per row, its loads in
         // flight together.  Fewer, longer rows (NCF: 1.9 K rows of 1.7 K plan
@@ -2746,6 +2805,7 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     pa.log2c = g.log2c;
     pa.cells = g.cells;
     pa.counted = planned;
+    pa.pairs = pairs;
     pa.row_launches = row_launches;
     pa.n = g.n;
     // large sketches (large round-0 frontiers) take round 0 on the whole chip
@@ -2774,8 +2834,11 @@ hipError_t launch_decode_t(const Geo& g, const void* plan, const void* y_agg_v,
     // and 1614; rows of 64 at 2^26 and 1 % 310 and 267.  A quarter of the CUs
     // writes at the full rate (48 of 256 workgroups 1124 us on the 2^30 case,
     // 64 945, 96 939, 128 959; the smaller cases are best at 24 to 64).
+    // Not in a sketch of less than half a cell per element, whose peel is over
+    // at once (30 M parameters, 1 %, 0.03 cells each, fp32: 117 and 137 us).
     uint32_t fill_groups = 0;
-    if (!in_place && out.x_out != nullptr && x_vec && mask_vec && L.cap <= g.n / 64) {
+    if (!in_place && out.x_out != nullptr && x_vec && mask_vec && L.cap <= g.n / 64 &&
+        2ull * g.cells >= L.cap) {
         fill_groups = (uint32_t)di.cus - peel_grid;
         if (fill_groups > (uint32_t)di.cus / 4u) fill_groups = (uint32_t)di.cus / 4u;
     }

@@ -14,14 +14,13 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
-def hot_support(n, c, rows, nbulk, seed):
-    """(ascending indices, the peelable ones' places among them, the hot cell's members)."""
+def hot_support(n, c, rows, free, nbulk, seed):
+    """(ascending indices, the places of those to be peeled among them)."""
     nb = n // c
     g = oracle.Geom(n=n, rows=rows, seed=seed, c=c)
     cl, _ = oracle.cells(g, np.arange(nb, dtype=np.uint64) * c)
     r = (cl // c).astype(np.int64)
     bias = (cl % c).astype(np.int64)
-    free = rows // 10
     hot = free  # the hot row; rows 0 .. free - 1 are the peelable elements' own
     bulk = np.nonzero((r > hot).all(1))[0][:nbulk]
     assert bulk.size == nbulk
@@ -30,13 +29,10 @@ def hot_support(n, c, rows, nbulk, seed):
     t = (0 - bias[b, j]) & (c - 1)  # the column that lands in the hot cell
     own = r[b] < free
     cell = r[b] * c + ((t[:, None] + bias[b]) & (c - 1))
-    # exactly one cell in the free rows, and no other element's
-    one = own.sum(1) == 1
-    fc = np.where(own, cell, 0).sum(1)
-    _, first = np.unique(fc, return_index=True)
-    pick = np.zeros(b.size, bool)
-    pick[first] = True
-    pick &= one
+    # cells in the free rows, one or two, that no other element has
+    cells, count = np.unique(cell[own], return_counts=True)
+    alone = np.isin(cell, cells[count == 1])
+    pick = own.any(1) & (alone | ~own).all(1)
     last = np.nonzero(own.sum(1) == 0)[0][0]  # both other cells among the bulk's
     e = np.concatenate([b[pick] * c + t[pick], [b[last] * c + t[last]]])
     idx = np.concatenate([(bulk[:, None] * c + np.arange(c)).reshape(-1), np.sort(e)])
@@ -44,23 +40,25 @@ def hot_support(n, c, rows, nbulk, seed):
 
 
 @pytest.mark.parametrize("vtype", ["f32", "i32"])
-@pytest.mark.parametrize("n,c,rows,pairs", [
-    (1 << 28, 1024, 1000, True),    # two workgroups to a row
-    (1 << 29, 1024, 2000, True),    # a workgroup per row
-    (1 << 28, 256, 4096, True),     # a wave per row
-    (1 << 28, 1024, 1000, False),   # more than 2^26 elements: fp32 counters stay integers
+@pytest.mark.parametrize("n,c,rows,free,support", [
+    # 1.2 cells per element or more: fp32 counters are doubles beside the residuals
+    (1 << 31, 1024, 900, 720, 750_000),      # two workgroups to a row
+    (1 << 31, 1024, 1300, 1040, 1_080_000),  # a workgroup per row
+    (1 << 31, 256, 5000, 4000, 1_030_000),   # a wave per row
+    # far fewer cells: fp32 counters and residuals in arrays of their own
+    (1 << 28, 1024, 1000, 100, 1 << 26),
+    (1 << 29, 1024, 2000, 200, 1 << 26),
+    (1 << 28, 256, 4096, 409, (1 << 26) + 12_000),
 ])
-def test_hot_cell(n, c, rows, pairs, vtype):
+def test_hot_cell(n, c, rows, free, support, vtype):
     import torch
     import paper_2402_07529_amd as hc
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     seed = 91
-    m26 = 1 << 26
-    nbulk = (m26 - 1000) // c if pairs else m26 // c + 10
-    idx, hot = hot_support(n, c, rows, nbulk, seed)
+    idx, hot = hot_support(n, c, rows, free, (support - 8000) // c, seed)
     m = idx.size
-    assert (m <= m26) == pairs
+    assert m <= support and (5 * rows * c >= 6 * m) == (support < 1 << 26)
     assert int(hot.sum()) >= 2**32  # the hot cell's positions
     print(f"n={n} c={c} rows={rows} support={m} hot={hot.size} {vtype}", flush=True)
     vt = torch.int32 if vtype == "i32" else torch.float32
